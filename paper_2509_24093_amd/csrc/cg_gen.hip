@@ -12,15 +12,10 @@ namespace cgdev {
 
 namespace {
 
-// Waves per SIMD the register allocation must allow.  Up to L_max = 6 the
-// inputs (2K complex values) fit a 256-register budget with at most a few
-// spills, and a second wave per SIMD hides the load latency of the first
-// (measured: 1.89 -> 1.26 ms at L_max = 6); L_max = 7, 8 need the whole
-// 512-entry file of one wave.
-constexpr int kMinWavesPerSimd = CGCONV_TU_L <= 6 ? 2 : 1;
-
+// Up to L_max = 6 the inputs of a point (2K complex values) fit one lane's
+// 256-register budget (two waves per SIMD) with at most a few spills.
 template <int L>
-__global__ __launch_bounds__(cgdev::kCgThreads, kMinWavesPerSimd) void cg_gen_kernel(CgArgs a) {
+__global__ __launch_bounds__(cgdev::kCgThreads, 2) void cg_gen_kernel(CgArgs a) {
   using namespace cgdev;
   constexpr int K = (L + 1) * (L + 1);
   const long long p = (long long)blockIdx.x * kCgThreads + threadIdx.x;
@@ -31,21 +26,28 @@ __global__ __launch_bounds__(cgdev::kCgThreads, kMinWavesPerSimd) void cg_gen_ke
   CgBody<L>::run(qa, ka, st);
 }
 
-// L_max 7 and 8: one point per pair of lanes (CgSplitBody), each lane with
-// K instead of 2K input values, so that two waves share a SIMD: a single
-// wave issues at most one instruction every ~4.8 cycles, two waves one every
-// ~2.4, which outweighs the larger operation count of the lane-pair form.
+// L_max 7 and 8: one point per pair of lanes (CgMirrorBody), so that two
+// waves share a SIMD (179 and 215 VGPRs, no scratch): a single wave issues at
+// most one instruction every ~4.8 cycles, two waves one every ~2.4.  Bound by
+// the vector instruction stream, 31.5k operations per lane at L_max = 8; the
+// lane pair that held q in one lane and k in the other took 39.8k.  Measured,
+// L_max = 8, B = 2, N = 65536, C = 64: 7.42 -> 6.36 ms; L_max = 7, B = 4, N =
+// 16384, C = 32: 1.19 -> 1.03 ms.  Below L_max = 7 one point per lane stays
+// faster, as its fewer instructions per point count for more than the third
+// wave a lane pair would allow (588 against 626 us at L_max = 6, 311 against
+// 344 at 5, B = 4, N = 16384, C = 32).
 template <int L>
 __global__ __launch_bounds__(cgdev::kCgThreads, 2) void cg_split_kernel(CgArgs a) {
   using namespace cgdev;
-  constexpr int K = (L + 1) * (L + 1);
+  constexpr int K = (L + 1) * (L + 1), H = (L + 1) * (L + 2) / 2;
   const long long lane = (long long)blockIdx.x * kCgThreads + threadIdx.x;
   const int half = (int)(lane & 1);
+  const float g = half ? -1.f : 1.f;
   const Point pt = point_of(lane >> 1, a);
-  float2 x[K];
-  load_unpack_half<K>(a, pt, half, x);
-  SplitPairStore st = make_split_store(a, pt, half, K);
-  CgSplitBody<L>::run(x, st);
+  float2 q[H], k[H];
+  load_unpack_mirror<L>(a, pt, half, g, q, k);
+  SplitPairStore st = make_split_store(a, pt, half, g, K);
+  CgMirrorBody<L>::run(q, k, st);
 }
 
 }  // namespace

@@ -260,10 +260,11 @@ __global__ __launch_bounds__(kMixThreads, 1) void cg_mix_kernel(CgArgs a) {
     __syncthreads();  // the mixed tiles are parked
     // this point's mixed complex-basis values w[J, M] (columns 32 J(J+1)/2 +
     // 16 (M+J) + 2 pt + {0, 1}), converted to the real basis and stored
-    // channel-pair packed as in the unmixed stage (half 0 writes)
+    // channel-pair packed as in the unmixed stage (half 0 writes the
+    // components M >= 0, half 1 those of M < 0)
     Point ps = pt;
     ps.valid = pt.valid && pt.c < 2 * a.Cp;
-    SplitPairStore out = make_split_store(a, ps, half, K);
+    SplitPairStore out = make_split_store(a, ps, half, half ? -1.f : 1.f, K);
     const float* base = smem + (2 * ptl) * G::RS + c;
     auto w_at = [&](int J, int M) {
       const float* e = base + (32 * (J * (J + 1) / 2) + 16 * (M + J)) * G::RS;
@@ -271,12 +272,12 @@ __global__ __launch_bounds__(kMixThreads, 1) void cg_mix_kernel(CgArgs a) {
     };
 #pragma unroll
     for (int J = 0; J <= L; ++J) {
-      out(J * J + J, w_at(J, 0));
+      out.store(J, 0, w_at(J, 0));
 #pragma unroll
       for (int mu = 1; mu <= J; ++mu) {
         const float2 wp = w_at(J, mu), wm = w_at(J, -mu);
-        out(J * J + J + mu, make_float2(wm.x + wp.x, wm.y + wp.y));  // U[J,+mu] = w[J,-mu] + w[J,+mu]
-        out(J * J + J - mu, make_float2(wm.y - wp.y, wp.x - wm.x));  // U[J,-mu] = i (w[J,+mu] - w[J,-mu])
+        // U[J,+mu] = w[J,-mu] + w[J,+mu], U[J,-mu] = i (w[J,+mu] - w[J,-mu])
+        out.store(J, mu, half ? make_float2(wm.y - wp.y, wp.x - wm.x) : make_float2(wm.x + wp.x, wm.y + wp.y));
       }
     }
   } else {

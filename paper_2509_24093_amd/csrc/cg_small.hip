@@ -15,9 +15,10 @@
 //      R1 x R2 (R1, R2 <= 16), a radix-R1 DFT in registers per (column, n2),
 //      the twiddle W_Nf^(n2 f1), a radix-R2 DFT per (column, f1); frequency
 //      f1 + R1 f2 ends at row R2 f1 + f2;
-//   3. one point (frequency pair w, N-w; channel) per pair of lanes: half 0
-//      gathers 2Q = A + conj B, half 1 (-1)^l 2K (A, B the spectra at w and
-//      N-w), and the lane-pair contraction CgSplitBody runs on registers;
+//   3. one point (frequency pair w, N-w; channel) per pair of lanes: both
+//      gather the spectra at w and N-w, half 0 keeps the complex-m components
+//      m >= 0 of 2Q and 2K, half 1 the mirrored ones, and the lane-pair
+//      contraction CgMirrorBody runs on registers;
 //   4. every output component, packed with the neighbouring channel
 //      (W = U_c + i U_{c+1} at row w, conj U_c + i conj U_{c+1} at row N-w),
 //      goes to an LDS tile [row][k][pair] that aliases the first one;
@@ -112,23 +113,19 @@ __device__ void dft_any(int lg, float2* Z, const float2* tw, int cols, uint32_t 
 // second radix of Nf = 2^lg as split above
 __device__ __forceinline__ int radix2_of(int lg) { return lg <= 4 ? 1 : (lg == 5 ? 4 : (lg <= 7 ? 8 : 16)); }
 
-// Output of one component: both halves of a point hold it after the sign
-// fix (half 1's combined value is (-1)^J times the output), so both write
-// the same value to the same slot; the channel partner is lane ^ 2.
+// Outputs of a lane pair: half 0 stores component (J, +mu), half 1 (J, -mu);
+// both hold the same value of (J, 0) and write it to the same slot.  The
+// channel partner is lane ^ 2.
 struct SmallStore {
   float2* V;    // LDS output tile [row][K][cq], row Nf = trash
   int K, cq, ci;
   int row;      // destination row of this lane (w, N - w), or Nf
-  float hsign;
+  float g;      // the half's sign
   bool even;
-  __device__ __forceinline__ void operator()(int kout, float2 u) const {
-    const int J = (int)__builtin_sqrtf((float)kout + 0.5f);
-    if (J & 1) {
-      u.x *= hsign;
-      u.y *= hsign;
-    }
+  __device__ __forceinline__ void put(int J, int mu, float2 acc) const {
+    const float2 u = mirror_out(J, mu, acc, g);
     const float2 v = make_float2(swap_quad_pair(u.x), swap_quad_pair(u.y));
-    V[((long long)row * K + kout) * cq + ci] =
+    V[((long long)row * K + J * J + J + (g < 0.f ? -mu : mu)) * cq + ci] =
         even ? make_float2(u.x - v.y, u.y + v.x) : make_float2(v.x + u.y, u.x - v.y);
   }
   __device__ __forceinline__ void end_phase(int) const {}
@@ -192,30 +189,24 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
     const int pc = valid ? p : 0;
     const int w = pc / cc, c = pc % cc;
     const int wn = (Nf - w) & (Nf - 1);
-    float2 x[K];
+    const float g = half ? -1.f : 1.f;
+    constexpr int H = (L + 1) * (L + 2) / 2;
+    float2 q[H], k[H];
     {
-      const float2* za = Z + (long long)row_of(w) * colsZ + c;
-      const float2* zb = Z + (long long)row_of(wn) * colsZ + c;
+      const float2* zv = Z + (long long)row_of(half ? wn : w) * colsZ + c;
+      const float2* zu = Z + (long long)row_of(half ? w : wn) * colsZ + c;
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const float2 A = za[k * cc], B = zb[k * cc];
-        int l = 0;
-        while ((l + 1) * (l + 1) <= k) ++l;  // compile-time after unrolling
-        const float sg = (l & 1) ? -1.f : 1.f;
-        x[k] = half ? make_float2(sg * (A.y + B.y), sg * (B.x - A.x)) : make_float2(A.x + B.x, A.y - B.y);
-        // opaque: the compiler may not recompute x[k] from the LDS values
-        asm volatile("" : "+v"(x[k].x), "+v"(x[k].y));
+      for (int l = 0; l <= L; ++l) {
+        mirror_unpack0(l, g, zv[(l * l + l) * cc], zu[(l * l + l) * cc], q[l * (l + 1) / 2], k[l * (l + 1) / 2]);
+#pragma unroll
+        for (int m = 1; m <= l; ++m) {
+          const int ic = (l * l + l + m) * cc, is = (l * l + l - m) * cc, h = l * (l + 1) / 2 + m;
+          mirror_unpack(l, g, zv[ic], zu[ic], zv[is], zu[is], q[h], k[h]);
+        }
       }
-    }
 #pragma unroll
-    for (int l = 1; l * l < K; ++l) {
-#pragma unroll
-      for (int mu = 1; mu <= l; ++mu) {
-        const int cs = l * l + l + mu, sn = l * l + l - mu;
-        const float2 xc = x[cs], xs = x[sn];
-        x[sn] = make_float2(xc.x - xs.y, xc.y + xs.x);
-        x[cs] = make_float2(xc.x + xs.y, xc.y - xs.x);
-      }
+      for (int h = 0; h < H; ++h)  // opaque: not recomputed from the LDS values
+        asm volatile("" : "+v"(q[h].x), "+v"(q[h].y), "+v"(k[h].x), "+v"(k[h].y));
     }
     __syncthreads();  // every lane has gathered: the output tile may overwrite Z
     SmallStore st;
@@ -224,12 +215,12 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
     st.cq = cq;
     st.ci = c >> 1;
     st.even = (c & 1) == 0;
-    st.hsign = half ? -1.f : 1.f;
+    st.g = g;
     // the odd channel of the self-paired frequencies 0 and Nf/2 would write
     // row w again with the conjugate: it writes the trash row instead
     const bool write = valid && (st.even || wn != w);
     st.row = write ? (st.even ? w : wn) : Nf;
-    CgSplitBody<L>::run(x, st);
+    CgMirrorBody<L>::run(q, k, st);
   }
   // 5. inverse DFT of every packed column, scale and store (time n at row
   // R2 (n mod R1) + n / R1)

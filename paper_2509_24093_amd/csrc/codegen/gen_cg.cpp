@@ -32,8 +32,8 @@
 // cg_common.h): written as ordinary C++, the compiler turns -(a*b) into
 // a*(-b) and keeps a negated copy of every input alive for the whole kernel.
 //
-// Further bodies per L: CgSplitBody<L>, the lane-pair form of the same
-// contraction (emit_split_body); CgPathSplitBody<L>, which keeps the paths
+// Further bodies per L: CgMirrorBody<L>, the lane-pair form of the same
+// contraction (emit_mirror_body); CgPathSplitBody<L>, which keeps the paths
 // apart for the channel-mixing kernel, in steps (emit_path_split_body); and
 // CgRealBody<L>, the token-wise real-basis product of the value tensor
 // product (emit_real_body).
@@ -176,65 +176,82 @@ void emit_half(Emitter& e, int M, const std::string& fixed,
   }
 }
 
+// Register names of a row's operands and the weight of its pairs: the fixed
+// component a = (l1, m1) of both inputs, the varying component b = (l2, m2),
+// and a factor on the coefficients of pair (l1, l2) (0: the pair is left out).
+struct RowOperands {
+  std::string qa, ka;
+  std::string (*qb)(int l, int m);
+  std::string (*kb)(int l, int m);
+  double (*weight)(int l1, int l2);
+};
+
+std::vector<Term> weighted(const std::vector<Term>& t, double w) {
+  std::vector<Term> r = t;
+  for (Term& x : r) x.coef *= w;
+  return r;
+}
+
 // Row l1 of the merged block (m1, m2 = M - m1), m1 <= m2: every pair
 // a = (l1, m1), b = (l2, m2) with l2 > l1 if m1 == m2 (the diagonal a == b
 // has a single term per J and takes the product form).
-void emit_row(Emitter& e, const TermMap& terms_of, int M, int l1, int m1, int m2) {
+void emit_row(Emitter& e, const TermMap& terms_of, int M, int l1, int m1, int m2, const RowOperands& op) {
   FILE* f = e.f;
   static const std::vector<Term> none;
   auto get = [&](int a, int b, int c, int d) -> const std::vector<Term>& {
     auto it = terms_of.find({a, b, c, d});
     return it == terms_of.end() ? none : it->second;
   };
-  if (m1 == m2) {
-    const std::vector<Term>& dg = get(l1, m1, l1, m1);
-    if (!dg.empty()) emit_half(e, M, qname(l1, m1), {{kname(l1, m1), &dg}});
+  if (m1 == m2 && op.weight(l1, l1) != 0.0) {
+    const std::vector<Term> dg = weighted(get(l1, m1, l1, m1), op.weight(l1, l1));
+    if (!dg.empty()) emit_half(e, M, op.qa, {{op.kb(l1, m1), &dg}});
   }
   // off-diagonal pairs of this row
   struct Pair {
     int l2;
-    const std::vector<Term>* x;  // terms of (a, b): qa[a] ka[b]
-    const std::vector<Term>* y;  // terms of (b, a): qa[b] ka[a]
+    std::vector<Term> x;  // terms of (a, b): qa[a] ka[b]
+    std::vector<Term> y;  // terms of (b, a): qa[b] ka[a]
   };
   std::vector<Pair> pairs;
   for (int l2 = std::abs(m2); l2 <= L_cur; ++l2) {
-    if (m1 == m2 && l2 <= l1) continue;
-    const std::vector<Term>& x = get(l1, m1, l2, m2);
-    const std::vector<Term>& y = get(l2, m2, l1, m1);
+    const double w = op.weight(l1, l2);
+    if ((m1 == m2 && l2 <= l1) || w == 0.0) continue;
+    const std::vector<Term> x = weighted(get(l1, m1, l2, m2), w);
+    const std::vector<Term> y = weighted(get(l2, m2, l1, m1), w);
     if (x.size() != y.size()) {
       std::fprintf(stderr, "gen_cg: swap partner missing (%d %d %d %d)\n", l1, m1, l2, m2);
       std::exit(1);
     }
-    if (!x.empty()) pairs.push_back({l2, &x, &y});
+    if (!x.empty()) pairs.push_back({l2, x, y});
   }
   if (pairs.empty()) return;
   long pair_cost = 0;
   std::vector<std::pair<int, const std::vector<Term>*>> xs, ys;
   for (const Pair& p : pairs) {
     bool ev = false, od = false;
-    for (const Term& t : *p.x) ((l1 + p.l2 - t.J) % 2 == 0 ? ev : od) = true;
-    pair_cost += (ev && od ? 12 : 8) + 2 * (long)p.x->size();
-    xs.push_back({p.l2, p.x});
-    ys.push_back({p.l2, p.y});
+    for (const Term& t : p.x) ((l1 + p.l2 - t.J) % 2 == 0 ? ev : od) = true;
+    pair_cost += (ev && od ? 12 : 8) + 2 * (long)p.x.size();
+    xs.push_back({p.l2, &p.x});
+    ys.push_back({p.l2, &p.y});
   }
   if (half_cost(xs) + half_cost(ys) < pair_cost) {
     std::vector<std::pair<std::string, const std::vector<Term>*>> xr, yr;
     for (const Pair& p : pairs) {
-      xr.push_back({kname(p.l2, m2), p.x});
-      yr.push_back({qname(p.l2, m2), p.y});
+      xr.push_back({op.kb(p.l2, m2), &p.x});
+      yr.push_back({op.qb(p.l2, m2), &p.y});
     }
-    emit_half(e, M, qname(l1, m1), xr);  // qa[a] * ka[b]
-    emit_half(e, M, kname(l1, m1), yr);  // ka[a] * qa[b]
+    emit_half(e, M, op.qa, xr);  // qa[a] * ka[b]
+    emit_half(e, M, op.ka, yr);  // ka[a] * qa[b]
     return;
   }
-  const std::string qa_ = qname(l1, m1), ka_ = kname(l1, m1);
+  const std::string &qa_ = op.qa, &ka_ = op.ka;
   for (const Pair& p : pairs) {
-    const std::string qb = qname(p.l2, m2), kb = kname(p.l2, m2);
+    const std::string qb = op.qb(p.l2, m2), kb = op.kb(p.l2, m2);
     bool ev = false, od = false;
-    for (const Term& t : *p.x) {
+    for (const Term& t : p.x) {
       // the two terms share the coefficient up to the swap sign
       const Term* u = nullptr;
-      for (const Term& w : *p.y)
+      for (const Term& w : p.y)
         if (w.J == t.J) u = &w;
       const double sigma = ((l1 + p.l2 - t.J) % 2 == 0) ? 1.0 : -1.0;
       if (!u || u->imag != t.imag || std::fabs(u->coef - sigma * t.coef) > 1e-12 * std::fabs(t.coef) + 1e-15) {
@@ -264,7 +281,7 @@ void emit_row(Emitter& e, const TermMap& terms_of, int M, int l1, int m1, int m2
                    qb.c_str(), ka_.c_str(), qb.c_str(), ka_.c_str(), qa_.c_str(), kb.c_str(), qa_.c_str(), kb.c_str());
       e.ops += 8;
     }
-    for (const Term& t : *p.x) {
+    for (const Term& t : p.x) {
       const bool even = (l1 + p.l2 - t.J) % 2 == 0;
       e.acc_add_scaled(acc_name(M, t.J), t.coef, t.imag, even ? "sr" : "dr", even ? "si" : "di");
     }
@@ -297,7 +314,9 @@ void emit_body(FILE* f, int L, long* ops_out) {
         if (m2 < -L || m2 > L || m1 > m2) continue;
         std::fprintf(f, "      // blocks m1=%d m2=%d and swapped\n", m1, m2);
         std::fprintf(f, "      {\n      const auto& kb = cg_kfence(ka);\n");
-        for (int l1 = std::abs(m1); l1 <= L; ++l1) emit_row(e, terms_of, M, l1, m1, m2);
+        for (int l1 = std::abs(m1); l1 <= L; ++l1)
+          emit_row(e, terms_of, M, l1, m1, m2,
+                   {qname(l1, m1), kname(l1, m1), qname, kname, [](int, int) { return 1.0; }});
         std::fprintf(f, "      }\n");
       }
     }
@@ -329,9 +348,9 @@ void emit_body(FILE* f, int L, long* ops_out) {
 }  // namespace
 
 // Lane-pair per-path body for the channel-mixing kernel
-// (CgPathSplitBody<L>): one point per pair of adjacent lanes as in
-// CgSplitBody (even lane x = qa, odd lane x[(l,m)] = (-1)^l ka[(l,m)]), the
-// products of every path kept apart.  The work is cut into pair steps over
+// (CgPathSplitBody<L>): one point per pair of adjacent lanes (even lane
+// x = qa, odd lane x[(l,m)] = (-1)^l ka[(l,m)]), the products of every path
+// kept apart.  The work is cut into pair steps over
 // unordered degree pairs {l1 <= l2}, each with a run Ja..Jb of output
 // degrees (at most kPairHalfSlots outputs (J, M) and kPairHalfPaths degrees).
 // In a step with l1 < l2 every product x[(l1,m1)] * partner(x[(l2,m2)]),
@@ -340,7 +359,7 @@ void emit_body(FILE* f, int L, long* ops_out) {
 // in the odd lane (swap symmetry c(q,o,J) = (-1)^(l1+l2-J) c(o,q,J), checked
 // for every pair): the two lanes evaluate the two ordered paths at once.  In
 // a step with l1 == l2 both ordered terms of an unordered pair belong to the
-// same path: as in CgSplitBody the lanes take one each (diagonal pairs half
+// same path: the lanes take one each (diagonal pairs half
 // the coefficient) and combine, w = acc + (-1)^J partner(acc).  Either way
 // the odd lane's value is (-1)^J times its path value; st.put<B, S0>(slot,
 // value, odd_J) corrects the sign and stages the value at slot (odd lanes
@@ -511,111 +530,84 @@ void emit_path_split_body(FILE* f, int L, long* ops_out) {
   *ops_out = e.ops;
 }
 
-// Lane-pair body for L_max 7 and 8 (CgSplitBody<L>::run(x, st)): one point
-// per pair of adjacent lanes, so that a lane holds K instead of 2K input
-// values and two waves fit on a SIMD.  The even lane holds x = qa, the odd
-// lane x[(l,m)] = (-1)^l ka[(l,m)], both in the complex-m basis.  For an
-// unordered component pair {o, q} one product p = x[o] * partner(x[q]) gives
-// the even lane (-1)^l_q qa[o] ka[q] (the term (o, q)) and the odd lane
-// (-1)^l_o qa[q] ka[o] (the term (q, o)).  Both lanes take the coefficient
-// (-1)^l_q c(o, q, J); by the swap symmetry c(q, o, J) =
-// (-1)^(l_o + l_q - J) c(o, q, J) the odd lane's sum is then (-1)^J times its
-// share of w[J, M], so w = acc + (-1)^J partner(acc) in the even lane.  A
-// diagonal pair (o == q) has terms of even J only and takes half its
-// coefficient in each lane.  Products are grouped by their partner factor,
-// fetched once per group (two lane-swap moves).  Per lane this is about
-// 2/3 of the single-lane body's operations, at half the registers.
-void emit_split_body(FILE* f, int L, long* ops_out) {
-  const int K = (L + 1) * (L + 1);
+// Mirror lane-pair body (CgMirrorBody<L>::run(q, k, st)): one point per pair
+// of adjacent lanes, which share the contraction by the sign of M.  The
+// coefficients obey c(l1 -m1, l2 -m2, J) = (-1)^(l1+l2-J) c(l1 m1, l2 m2, J)
+// (checked here for every term), so the outputs w[J, -M] are the outputs
+// w[J, +M] of the mirrored inputs up to signs of the degrees.  The even lane
+// holds the components m >= 0 of both inputs, q[l,m] = qa[l,m], the odd lane
+// the mirrored ones, q[l,m] = (-1)^l qa[l,-m] (k alike): (L+1)(L+2)/2 instead
+// of (L+1)^2 components each.  Both run the same instructions for
+// the phases M = mu >= 0: the even lane's sum is w[J,mu], the odd lane's
+// (-1)^J w[J,-mu].  A component of m < 0 is the partner lane's value of +m
+// times (-1)^l (a lane swap, once per row; the sign goes into the
+// coefficients).  Of the phase mu = 0, whose pairs of components mirror into
+// each other, each lane takes the pairs {(l1,-a), (l2,a)} with l1 < l2 and
+// half the weight of the self-mirrored ones.  st.put(J, mu, acc) receives
+// both lanes' sums (mirror_out in cg_common.h turns them into the real-basis
+// outputs).  Per lane this is 1.04-1.1 times half the single-lane body's
+// operations, with 4 (L+1)(L+2)/2 input floats instead of 4 (L+1)^2.
+int hidx(int l, int m) { return l * (l + 1) / 2 + m; }
+std::string mqname(int l, int m) { return "q[" + std::to_string(hidx(l, m)) + "]"; }
+std::string mkname(int l, int m) { return "k[" + std::to_string(hidx(l, m)) + "]"; }
+
+void emit_mirror_body(FILE* f, int L, long* ops_out) {
+  const int H = (L + 1) * (L + 2) / 2;
   std::vector<Term> terms = contraction_terms(L);
   TermMap terms_of;
   for (const Term& t : terms) terms_of[{t.l1, t.m1, t.l2, t.m2}].push_back(t);
-  L_cur = L;
-  auto lm = [](int c, int& l, int& m) {
-    l = 0;
-    while ((l + 1) * (l + 1) <= c) ++l;
-    m = c - l * l - l;
-  };
-  Emitter e{f, {}, 0};
-  std::fprintf(f, "template <>\nstruct CgSplitBody<%d> {\n  static constexpr int K = %d;\n", L, K);
-  std::fprintf(f, "  template <class Store>\n");
-  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&x)[%d], Store& st) {\n", K);
-  for (int mu = 0; mu <= L; ++mu) {
-    std::fprintf(f, "    {  // phase |M| = %d\n", mu);
-    std::vector<int> Ms = mu == 0 ? std::vector<int>{0} : std::vector<int>{mu, -mu};
-    for (int M : Ms)
-      for (int J = mu; J <= L; ++J) std::fprintf(f, "      float2 %s;\n", acc_name(M, J).c_str());
-    // unordered pairs {o < q} and diagonals of this phase, grouped by q
-    std::map<int, std::vector<int>> groups;
-    for (const auto& kv : terms_of) {
-      const int o = comp(kv.first[0], kv.first[1]), q = comp(kv.first[2], kv.first[3]);
-      const int M = kv.first[1] + kv.first[3];
-      if (std::find(Ms.begin(), Ms.end(), M) == Ms.end() || o > q) continue;
-      if (o != q) {
-        auto it = terms_of.find({kv.first[2], kv.first[3], kv.first[0], kv.first[1]});
-        if (it == terms_of.end() || it->second.size() != kv.second.size()) {
-          std::fprintf(stderr, "gen_cg: swap partner missing (split body)\n");
-          std::exit(1);
-        }
-        for (const Term& t : kv.second) {
-          const Term* u = nullptr;
-          for (const Term& w : it->second)
-            if (w.J == t.J) u = &w;
-          const double sigma = ((t.l1 + t.l2 - t.J) % 2 == 0) ? 1.0 : -1.0;
-          if (!u || u->imag != t.imag || std::fabs(u->coef - sigma * t.coef) > 1e-12 * std::fabs(t.coef) + 1e-15) {
-            std::fprintf(stderr, "gen_cg: swap symmetry violated (split body)\n");
-            std::exit(1);
-          }
-        }
-      } else {
-        for (const Term& t : kv.second)
-          if (t.J % 2 != 0) {
-            std::fprintf(stderr, "gen_cg: diagonal term of odd J (split body)\n");
-            std::exit(1);
-          }
-      }
-      groups[q].push_back(o);
+  for (const Term& t : terms) {
+    const double sg = ((t.l1 + t.l2 - t.J) % 2 == 0) ? 1.0 : -1.0;
+    bool ok = false;
+    for (const Term& u : terms_of[{t.l1, -t.m1, t.l2, -t.m2}])
+      if (u.J == t.J) ok = u.imag == t.imag && std::fabs(u.coef - sg * t.coef) <= 1e-12 * std::fabs(t.coef) + 1e-15;
+    if (!ok) {
+      std::fprintf(stderr, "gen_cg: mirror symmetry violated (%d %d %d %d J=%d)\n", t.l1, t.m1, t.l2, t.m2, t.J);
+      std::exit(1);
     }
-    for (const auto& g : groups) {
-      const int q = g.first;
-      int lq, mq;
-      lm(q, lq, mq);
-      std::fprintf(f, "      { const float2 pq = lane_partner2(x[%d]);\n", q);
-      e.ops += 2;
-      for (int o : g.second) {
-        int lo, mo;
-        lm(o, lo, mo);
-        std::fprintf(f, "      { const float pr = fnma(x[%d].y, pq.y, x[%d].x * pq.x);", o, o);
-        std::fprintf(f, " const float pi = fmaf(x[%d].y, pq.x, x[%d].x * pq.y);\n", o, o);
+  }
+  L_cur = L;
+  Emitter e{f, {}, 0};
+  std::fprintf(f, "template <>\nstruct CgMirrorBody<%d> {\n  static constexpr int H = %d;\n", L, H);
+  std::fprintf(f, "  template <class Store>\n");
+  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&q)[%d], const float2 (&k)[%d], Store& st) {\n",
+               H, H);
+  for (int mu = 0; mu <= L; ++mu) {
+    std::fprintf(f, "    {  // phase M = %d\n", mu);
+    for (int J = mu; J <= L; ++J) std::fprintf(f, "      float2 %s;\n", acc_name(mu, J).c_str());
+    for (int m1 = mu - L; 2 * m1 <= mu; ++m1) {
+      const int m2 = mu - m1;
+      std::fprintf(f, "      // blocks m1=%d m2=%d and swapped\n", m1, m2);
+      for (int l1 = std::abs(m1); l1 <= L; ++l1) {
+        if (m1 >= 0) {
+          if (mu == 0)
+            emit_row(e, terms_of, mu, l1, m1, m2,
+                     {mqname(l1, m1), mkname(l1, m1), mqname, mkname, [](int, int) { return 0.5; }});
+          else
+            emit_row(e, terms_of, mu, l1, m1, m2,
+                     {mqname(l1, m1), mkname(l1, m1), mqname, mkname, [](int, int) { return 1.0; }});
+          continue;
+        }
+        std::fprintf(f, "      { float2 fq, fk; lane_partner4(%s, %s, fq, fk);\n", mqname(l1, -m1).c_str(),
+                     mkname(l1, -m1).c_str());
         e.ops += 4;
-        const double scale = ((lq % 2) ? -1.0 : 1.0) * (o == q ? 0.5 : 1.0);
-        for (const Term& t : terms_of.at({lo, mo, lq, mq}))
-          e.acc_add_scaled(acc_name(t.M, t.J), scale * t.coef, t.imag, "pr", "pi");
+        if (mu == 0)
+          emit_row(e, terms_of, mu, l1, m1, m2, {"fq", "fk", mqname, mkname, [](int a, int b) {
+                                                   const double s = (a % 2) ? -1.0 : 1.0;
+                                                   return b < a ? 0.0 : (b == a ? 0.5 * s : s);
+                                                 }});
+        else
+          emit_row(e, terms_of, mu, l1, m1, m2,
+                   {"fq", "fk", mqname, mkname, [](int a, int) { return (a % 2) ? -1.0 : 1.0; }});
         std::fprintf(f, "      }\n");
       }
-      std::fprintf(f, "      }\n");
       std::fprintf(f, "      __builtin_amdgcn_sched_barrier(0);\n");
     }
-    // the even lane's w = acc + (-1)^J partner(acc), then the real basis
     for (int J = mu; J <= L; ++J) {
-      for (int M : Ms) {
-        const std::string a = acc_name(M, J);
-        if (!e.inited.count(a)) std::fprintf(f, "      %s = make_float2(0.f, 0.f);\n", a.c_str());
-        const char* op = J % 2 ? "-" : "+";
-        std::fprintf(f, "      %s.x = %s.x %s lane_partner(%s.x); %s.y = %s.y %s lane_partner(%s.y);\n", a.c_str(),
-                     a.c_str(), op, a.c_str(), a.c_str(), a.c_str(), op, a.c_str());
-        e.ops += 2;
-      }
-      if (mu == 0) {
-        std::fprintf(f, "      st(%d, %s);\n", comp(J, 0), acc_name(0, J).c_str());
-      } else {
-        const std::string p = acc_name(mu, J), m = acc_name(-mu, J);
-        std::fprintf(f, "      st(%d, make_float2(%s.x + %s.x, %s.y + %s.y));\n", comp(J, mu), m.c_str(),
-                     p.c_str(), m.c_str(), p.c_str());
-        std::fprintf(f, "      st(%d, make_float2(%s.y - %s.y, %s.x - %s.x));\n", comp(J, -mu), m.c_str(),
-                     p.c_str(), p.c_str(), m.c_str());
-        e.ops += 4;
-      }
+      const std::string a = acc_name(mu, J);
+      if (!e.inited.count(a)) std::fprintf(f, "      %s = make_float2(0.f, 0.f);\n", a.c_str());
+      std::fprintf(f, "      st.put(%d, %d, %s);\n", J, mu, a.c_str());
+      e.ops += 6;
     }
     e.inited.clear();
     std::fprintf(f, "      st.end_phase(%d);\n", mu);
@@ -721,11 +713,11 @@ int main(int argc, char** argv) {
     long ops = 0, rops = 0, sops = 0, psops = 0;
     emit_body(f, L, &ops);
     emit_real_body(f, L, &rops);
-    emit_split_body(f, L, &sops);
+    emit_mirror_body(f, L, &sops);
     emit_path_split_body(f, L, &psops);
     std::fclose(f);
     std::fprintf(stderr,
-                 "gen_cg: L=%d ops/point=%ld real token-wise ops=%ld lane-pair ops/lane=%ld "
+                 "gen_cg: L=%d ops/point=%ld real token-wise ops=%ld mirror lane-pair ops/lane=%ld "
                  "per-path lane-pair ops/lane=%ld\n",
                  L, ops, rops, sops, psops);
   }

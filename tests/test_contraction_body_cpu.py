@@ -1,0 +1,125 @@
+"""The generated contraction bodies evaluated on the CPU (no GPU): the code
+generator's output is compiled as host C++ with double precision in place of
+float and compared with the plan's host contraction of the same table
+(cgconv_contract_host), which is itself pinned to the oracle's dense tensor.
+The mirror lane-pair body runs with both lanes of a point side by side: a
+value is a pair of doubles, one per lane, and the lane swap exchanges them.
+"""
+
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2509_24093_amd as P
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_24093_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(not os.path.exists(P.LIB_PATH), reason="libcgconv.so not built")
+
+PRELUDE = r"""
+#include <cmath>
+#define __device__
+#define __forceinline__ inline
+#define __builtin_amdgcn_sched_barrier(x)
+struct V { double a, b; V() = default; V(double x) : a(x), b(x) {} V(double x, double y) : a(x), b(y) {} };
+static inline V operator*(V x, V y) { return V(x.a * y.a, x.b * y.b); }
+static inline V operator+(V x, V y) { return V(x.a + y.a, x.b + y.b); }
+static inline V operator-(V x, V y) { return V(x.a - y.a, x.b - y.b); }
+static inline V operator-(V x) { return V(-x.a, -x.b); }
+static inline V vfma(V x, V y, V z) { return x * y + z; }
+static inline V fnma(V x, V y, V z) { return z - x * y; }
+#define float V
+#define fmaf vfma
+struct float2 { V x, y; };
+static inline float2 make_float2(V x, V y) { return {x, y}; }
+static inline V sw(V v) { return V(v.b, v.a); }
+static inline V lane_partner(V v) { return sw(v); }
+static inline float2 lane_partner2(float2 v) { return {sw(v.x), sw(v.y)}; }
+static inline void lane_partner4(float2 a, float2 b, float2& pa, float2& pb) { pa = lane_partner2(a); pb = lane_partner2(b); }
+template <class T> static inline const T& cg_kfence(const T& k) { return k; }
+template <int L> struct CgBody;
+template <int L> struct CgRealBody;
+template <int L> struct CgMirrorBody;
+template <int L> struct CgPathSplitBody;
+"""
+
+DRIVER = r"""
+// mirror body: x = qa, ka in the complex-m basis (K complex values each), out = U (K complex values)
+struct MStore {
+  double* out;
+  void put(int J, int mu, float2 acc) {
+    const double s = (J & 1) ? -1 : 1;
+    const double wpx = acc.x.a, wpy = acc.y.a, wmx = s * acc.x.b, wmy = s * acc.y.b;
+    double* p = out + 2 * (J * J + J + mu);
+    if (mu == 0) { p[0] = wpx + wmx; p[1] = wpy + wmy; return; }
+    double* n = out + 2 * (J * J + J - mu);
+    p[0] = wpx + wmx; p[1] = wpy + wmy;
+    n[0] = -(wpy - wmy); n[1] = wpx - wmx;
+  }
+  void end_phase(int) {}
+};
+extern "C" void mirror(const double* qa, const double* ka, double* out) {
+  constexpr int H = (LL + 1) * (LL + 2) / 2;
+  float2 q[H], k[H];
+  for (int l = 0; l <= LL; ++l)
+    for (int m = 0; m <= l; ++m) {
+      const int p = 2 * (l * l + l + m), n = 2 * (l * l + l - m), h = l * (l + 1) / 2 + m;
+      const double s = (l & 1) ? -1 : 1;
+      q[h] = {V(qa[p], s * qa[n]), V(qa[p + 1], s * qa[n + 1])};
+      k[h] = {V(ka[p], s * ka[n]), V(ka[p + 1], s * ka[n + 1])};
+    }
+  MStore st{out};
+  CgMirrorBody<LL>::run(q, k, st);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def bodies(tmp_path_factory):
+    d = tmp_path_factory.mktemp("bodies")
+    subprocess.run(["g++", "-O1", "-std=c++17", os.path.join(CSRC, "codegen", "gen_cg.cpp"),
+                    os.path.join(CSRC, "cg_table.cpp"), "-o", str(d / "gen")], check=True)
+    subprocess.run([str(d / "gen"), str(d), "8"], check=True, capture_output=True)
+
+    def load(L):
+        src = d / f"b{L}.cpp"
+        src.write_text(PRELUDE + f'#define LL {L}\n#include "cg_body_L{L}.inc"\n#undef float\n' + DRIVER)
+        so = d / f"b{L}.so"
+        subprocess.run(["g++", "-O0", "-std=c++17", "-w", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+        return ctypes.CDLL(str(so))
+
+    return load
+
+
+def _complex_basis(L, x):
+    """2x in the complex-m basis: a[l,-mu] = x_c + i x_s, a[l,+mu] = x_c - i x_s."""
+    a = np.array(2 * x)
+    for l in range(1, L + 1):
+        for mu in range(1, l + 1):
+            c, s = l * l + l + mu, l * l + l - mu
+            a[s], a[c] = 2 * (x[c] + 1j * x[s]), 2 * (x[c] - 1j * x[s])
+    return a
+
+
+def _ptr(a):
+    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+
+
+@pytest.mark.parametrize("L", [0, 1, 2, 5, 7, 8])
+def test_mirror_body_is_the_host_contraction(L, bodies):
+    lib = bodies(L)
+    rng = np.random.default_rng(40 + L)
+    K = (L + 1) ** 2
+    for _ in range(2):
+        q = rng.normal(size=K) + 1j * rng.normal(size=K)
+        k = rng.normal(size=K) + 1j * rng.normal(size=K)
+        qa, ka = _complex_basis(L, q), _complex_basis(L, k)
+        out = np.zeros(K, dtype=np.complex128)
+        lib.mirror(_ptr(qa), _ptr(ka), _ptr(out))
+        ref = P.cgconv_contract_host(L, q, k)
+        # the emitted coefficients are rounded to float (2^-24 each)
+        assert np.abs(out - ref).max() < 2e-7 * np.abs(ref).max() * np.sqrt(K)
