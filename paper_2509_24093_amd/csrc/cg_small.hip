@@ -25,7 +25,13 @@
 //   5. inverse DFT of every column (k, pair) in the same way (time n1 + R1 n2
 //      at row R2 n1 + n2), x 1/Nf, and the store of the real and imaginary
 //      parts as channels c and c+1.
-// HBM traffic is q, k in and out out; the kernel is one launch.
+// HBM traffic is q, k in and out out; the kernel is one launch, also for the
+// two gradients of a backward (the adjoint form, one problem each).
+// Bound by latency: one lane's chain of loads, LDS exchanges and dependent
+// operations (of 47k cycles at B=32, N=32, L_max=4, C=32 with one lane group
+// per point, 20k were the contraction's 2.6k operations, which two groups
+// halve).  Measured at that shape: forward 23.7 -> 19.4 us, both gradients
+// 52.5 us in six launches of the three kernels -> 23.3 us.
 #include <hip/hip_runtime.h>
 
 #include "cg_common.h"
@@ -67,16 +73,16 @@ __device__ void dft_columns(float2* Z, const float2* tw, int cols, uint32_t mc, 
   // stage 1: per (column, n2), rows R2 n1 + n2 -> radix R1 -> x W^(n2 f1)
   for (int it = tid; it < R2 * cols; it += nthreads) {
     const int n2 = divm(it, mc), col = it - n2 * cols;
-    float2* z = Z + (long long)n2 * cols + col;
+    float2* z = Z + n2 * cols + col;
     float2 x[R1];
 #pragma unroll
-    for (int t = 0; t < R1; ++t) x[t] = z[(long long)t * R2 * cols];
+    for (int t = 0; t < R1; ++t) x[t] = z[t * R2 * cols];
     dft::dft_reg<R1, DIR>(x);
 #pragma unroll
     for (int f = 0; f < R1; ++f) {
       float2 w = tw[n2 * f];
       if (DIR > 0) w.y = -w.y;
-      z[(long long)f * R2 * cols] = f == 0 ? x[0] : cmulf(x[f], w);
+      z[f * R2 * cols] = f == 0 ? x[0] : cmulf(x[f], w);
     }
   }
   if constexpr (R2 > 1) {
@@ -84,13 +90,13 @@ __device__ void dft_columns(float2* Z, const float2* tw, int cols, uint32_t mc, 
     // stage 2: per (column, f1), rows R2 f1 .. R2 f1 + R2 - 1 -> radix R2, in place
     for (int it = tid; it < R1 * cols; it += nthreads) {
       const int f1 = divm(it, mc), col = it - f1 * cols;
-      float2* z = Z + (long long)f1 * R2 * cols + col;
+      float2* z = Z + f1 * R2 * cols + col;
       float2 x[R2];
 #pragma unroll
-      for (int t = 0; t < R2; ++t) x[t] = z[(long long)t * cols];
+      for (int t = 0; t < R2; ++t) x[t] = z[t * cols];
       dft::dft_reg<R2, DIR>(x);
 #pragma unroll
-      for (int f = 0; f < R2; ++f) z[(long long)f * cols] = x[f];
+      for (int f = 0; f < R2; ++f) z[f * cols] = x[f];
     }
   }
   __syncthreads();
@@ -125,7 +131,7 @@ struct SmallStore {
   __device__ __forceinline__ void put(int J, int mu, float2 acc) const {
     const float2 u = mirror_out(J, mu, acc, g);
     const float2 v = make_float2(swap_quad_pair(u.x), swap_quad_pair(u.y));
-    V[((long long)row * K + J * J + J + (g < 0.f ? -mu : mu)) * cq + ci] =
+    V[(row * K + J * J + J + (g < 0.f ? -mu : mu)) * cq + ci] =
         even ? make_float2(u.x - v.y, u.y + v.x) : make_float2(v.x + u.y, u.x - v.y);
   }
   __device__ __forceinline__ void end_phase(int) const {}
@@ -139,38 +145,46 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
   const int tid = threadIdx.x, nthreads = blockDim.x;
   const int b = blockIdx.x / a.groups, grp = blockIdx.x % a.groups;
   const int c0 = grp * cc;  // first channel of the group
-  float2* Z = smem;                             // [Nf][K][cc]
-  float2* tw = smem + (long long)Nf * K * cc;   // [Nf]
+  const SmallProblem pr = a.problem[blockIdx.y];
+  float2* Z = smem;                 // [Nf][K][cc]
+  float2* tw = smem + Nf * K * cc;  // [Nf]
   const int colsZ = K * cc, colsV = K * cq;
 
   for (int j = tid; j < Nf; j += nthreads) tw[j] = a.tw[j];
-  // 1. load q + i k: eight elements per thread in flight
+  // 1. load q + i k: kInFlight elements per thread at a time.  The adjoint
+  // form (pr.scales) scales both operands per component and reads the rows
+  // of the second one reversed.
+  constexpr int kInFlight = 8;
   const long long in_b = (long long)b * a.in_rows * K * a.C;
   const int totalZ = Nf * colsZ;
-  for (int base = 0; base < totalZ; base += 8 * nthreads) {
-    float2 z[8];
+  const bool adj = pr.scales != nullptr;
+  for (int base = 0; base < totalZ; base += kInFlight * nthreads) {
+    float2 z[kInFlight], sc[kInFlight];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kInFlight; ++u) {
       const int it = base + u * nthreads + tid;
       const int n = divm(it, a.mz), col = it - n * colsZ;
       const int k = col >> a.lcc, c = col & (cc - 1);
       const int ch = c0 + c < a.C ? c0 + c : a.C - 1;
+      const int n1 = adj ? (-n) & (Nf - 1) : n;
       z[u] = make_float2(0.f, 0.f);
-      if (it < totalZ && n < a.in_rows) {
-        const long long off = in_b + ((long long)n * K + k) * a.C + ch;
-        if (a.bf16) {
-          const uint16_t* q16 = static_cast<const uint16_t*>(a.q);
-          const uint16_t* k16 = static_cast<const uint16_t*>(a.k);
-          z[u] = make_float2(__uint_as_float((uint32_t)q16[off] << 16), __uint_as_float((uint32_t)k16[off] << 16));
-        } else {
-          z[u] = make_float2(static_cast<const float*>(a.q)[off], static_cast<const float*>(a.k)[off]);
-        }
+      const bool in0 = it < totalZ && n < a.in_rows, in1 = it < totalZ && n1 < a.in_rows;
+      const uint32_t off0 = ((uint32_t)n * K + k) * (uint32_t)a.C + ch, off1 = ((uint32_t)n1 * K + k) * (uint32_t)a.C + ch;
+      if (a.bf16) {
+        const uint16_t* q16 = static_cast<const uint16_t*>(pr.q) + in_b;
+        const uint16_t* k16 = static_cast<const uint16_t*>(pr.k) + in_b;
+        if (in0) z[u].x = __uint_as_float((uint32_t)q16[off0] << 16);
+        if (in1) z[u].y = __uint_as_float((uint32_t)k16[off1] << 16);
+      } else {
+        if (in0) z[u].x = (static_cast<const float*>(pr.q) + in_b)[off0];
+        if (in1) z[u].y = (static_cast<const float*>(pr.k) + in_b)[off1];
       }
+      if (adj && it < totalZ) sc[u] = make_float2(pr.scales[k], pr.scales[K + k]);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kInFlight; ++u) {
       const int it = base + u * nthreads + tid;
-      if (it < totalZ) Z[it] = z[u];
+      if (it < totalZ) Z[it] = adj ? make_float2(z[u].x * sc[u].x, z[u].y * sc[u].y) : z[u];
     }
   }
   // 2. forward DFT of every column
@@ -178,23 +192,28 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
   const int R1 = Nf / radix2_of(lg), R2 = radix2_of(lg);
   auto row_of = [&](int f) { return R2 * (f & (R1 - 1)) + (f / R1); };  // row of frequency f
 
-  // 3. gather and contract: point p = (w, c) on lanes 2p, 2p + 1 (the
-  // block has a lane for every point; lanes past the last point repeat
-  // point 0 and write the trash row)
+  // 3. gather and contract: point p = (w, c) on lanes 2p, 2p + 1 of each
+  // part (a part has a lane for every point; lanes past the last point repeat
+  // point 0 and write the trash row).  Every part gathers the same inputs and
+  // takes its own phases |M|: a lane's chain of dependent operations is what
+  // the block waits for here.
   {
     const int npts = ((Nf >> 1) + 1) * cc;
-    const int half = tid & 1;
-    const int p = tid >> 1;
+    const int lanes = nthreads / a.parts;  // whole waves
+    const int part = __builtin_amdgcn_readfirstlane(tid / lanes);
+    const int lt = tid - part * lanes;
+    const int half = lt & 1;
+    const int p = lt >> 1;
     const bool valid = p < npts;
     const int pc = valid ? p : 0;
-    const int w = pc / cc, c = pc % cc;
+    const int w = pc >> a.lcc, c = pc & (cc - 1);
     const int wn = (Nf - w) & (Nf - 1);
     const float g = half ? -1.f : 1.f;
     constexpr int H = (L + 1) * (L + 2) / 2;
     float2 q[H], k[H];
     {
-      const float2* zv = Z + (long long)row_of(half ? wn : w) * colsZ + c;
-      const float2* zu = Z + (long long)row_of(half ? w : wn) * colsZ + c;
+      const float2* zv = Z + row_of(half ? wn : w) * colsZ + c;
+      const float2* zu = Z + row_of(half ? w : wn) * colsZ + c;
 #pragma unroll
       for (int l = 0; l <= L; ++l) {
         mirror_unpack0(l, g, zv[(l * l + l) * cc], zu[(l * l + l) * cc], q[l * (l + 1) / 2], k[l * (l + 1) / 2]);
@@ -220,7 +239,7 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
     // row w again with the conjugate: it writes the trash row instead
     const bool write = valid && (st.even || wn != w);
     st.row = write ? (st.even ? w : wn) : Nf;
-    CgMirrorBody<L>::run(q, k, st);
+    CgMirrorBody<L>::run(q, k, st, a.phases[part]);
   }
   // 5. inverse DFT of every packed column, scale and store (time n at row
   // R2 (n mod R1) + n / R1)
@@ -228,20 +247,33 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
   const float inv = 1.0f / (float)Nf;
   const long long out_b = (long long)b * a.out_rows * K * a.C;
   const int totalV = a.out_rows * colsV;
+  const bool even_c = (a.C & 1) == 0;
+#pragma unroll 4
   for (int it = tid; it < totalV; it += nthreads) {
     const int n = divm(it, a.mv), col = it - n * colsV;
     const int k = col >> (a.lcc - 1), pi = col & (cq - 1);
-    const float2 v = Z[(long long)row_of(n) * colsV + col];
+    float2 v = Z[row_of(n) * colsV + col];
+    v.x *= inv;
+    v.y *= inv;
+    if (adj) {
+      const float so = pr.scales[2 * K + k];
+      v.x *= so;
+      v.y *= so;
+    }
     const int ch = c0 + 2 * pi;
-    const long long off = out_b + ((long long)n * K + k) * a.C + ch;
+    const uint32_t off = ((uint32_t)n * K + k) * (uint32_t)a.C + ch;
     if (a.bf16) {
-      uint16_t* o16 = static_cast<uint16_t*>(a.out);
-      if (ch < a.C) o16[off] = f32_to_bf16_rne(v.x * inv);
-      if (ch + 1 < a.C) o16[off + 1] = f32_to_bf16_rne(v.y * inv);
+      uint16_t* o16 = static_cast<uint16_t*>(pr.out) + out_b;
+      if (ch < a.C) o16[off] = f32_to_bf16_rne(v.x);
+      if (ch + 1 < a.C) o16[off + 1] = f32_to_bf16_rne(v.y);
     } else {
-      float* o = static_cast<float*>(a.out);
-      if (ch < a.C) o[off] = v.x * inv;
-      if (ch + 1 < a.C) o[off + 1] = v.y * inv;
+      float* o = static_cast<float*>(pr.out) + out_b;
+      if (even_c) {
+        if (ch < a.C) *reinterpret_cast<float2*>(o + off) = v;  // ch and off are even
+      } else {
+        if (ch < a.C) o[off] = v.x;
+        if (ch + 1 < a.C) o[off + 1] = v.y;
+      }
     }
   }
 }
@@ -254,12 +286,31 @@ hipError_t launch_cg_small<CGCONV_TU_L>(const SmallArgs& a, hipStream_t s) {
   const int cc = 1 << a.lcc;
   if (a.Nf < 2 || a.Nf > kSmallMaxNf || (1 << a.lg) != a.Nf || a.lcc < 1 || a.lcc > 4 || a.cc != cc ||
       a.threads < 64 || a.threads > small_max_threads(CGCONV_TU_L) || (a.threads & 63) ||
-      2 * ((a.Nf / 2 + 1) * cc) > a.threads || a.groups != (a.C + cc - 1) / cc || a.in_rows > a.Nf ||
+      a.parts < 1 || a.parts > kSmallMaxParts || a.threads % (64 * a.parts) != 0 || 2 * ((a.Nf / 2 + 1) * cc) * a.parts > a.threads ||
+      a.problems < 1 || a.problems > 2 || a.groups != (a.C + cc - 1) / cc || a.in_rows > a.Nf ||
       a.out_rows > a.Nf || a.mz != 0xFFFFFFFFu / (uint32_t)(K * cc) + 1 || a.mv != 0xFFFFFFFFu / (uint32_t)(K * cc / 2) + 1)
     return hipErrorInvalidValue;
   const size_t lds = ((size_t)a.Nf * K * cc + a.Nf) * sizeof(float2);
   if (lds > kSmallMaxLds) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(cg_small_kernel<CGCONV_TU_L>, dim3((unsigned)(a.B * a.groups)), dim3(a.threads), lds, s, a);
+  // the phases of each part: the longest first, each to the part with the
+  // least work so far
+  SmallArgs args = a;
+  using Body = cgdev::CgMirrorBody<CGCONV_TU_L>;
+  long work[kSmallMaxParts] = {};
+  unsigned left = (2u << CGCONV_TU_L) - 1;
+  for (int i = 0; i < kSmallMaxParts; ++i) args.phases[i] = 0;
+  while (left) {
+    int mu = -1, part = 0;
+    for (int m = 0; m <= CGCONV_TU_L; ++m)
+      if ((left >> m & 1) && (mu < 0 || Body::kPhaseOps[m] > Body::kPhaseOps[mu])) mu = m;
+    for (int i = 1; i < a.parts; ++i)
+      if (work[i] < work[part]) part = i;
+    work[part] += Body::kPhaseOps[mu];
+    args.phases[part] |= 1u << mu;
+    left &= ~(1u << mu);
+  }
+  hipLaunchKernelGGL(cg_small_kernel<CGCONV_TU_L>, dim3((unsigned)(a.B * a.groups), a.problems), dim3(a.threads), lds,
+                     s, args);
   return hipGetLastError();
 }
 

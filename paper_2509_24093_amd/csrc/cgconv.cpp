@@ -73,8 +73,10 @@ struct cgconv_plan {
   int L = 0, K = 0;
   int64_t N1 = 0, N2 = 0;  // N1 == 0: single pass
   bool fused = false;      // two-pass with N2 = 64 and the fused middle kernel
-  bool small = false;      // DFT length <= 256: the forward is one block per channel group (cg_small.hip)
-  int small_cc = 0, small_threads = 0;
+  // DFT length <= 256: the forward / the backward is one block per channel
+  // group (cg_small.hip) of small_cc channels, small_lanes threads per part
+  bool small_fwd = false, small_bwd = false;
+  int small_cc = 0, small_lanes = 0;
   int device = 0;
   int64_t nnz = 0, paths = 0, products = 0;  // nnz: complex-basis terms the contraction evaluates
   // the real-basis tensor the plan's kernels evaluate (cgconv_plan_export_table)
@@ -282,6 +284,40 @@ PassArgs base_args(const cgconv_plan* p) {
   return a;
 }
 
+// The one-block kernel for n (1 or 2) convolutions of the plan's shape.
+hipError_t run_small(const cgconv_plan* p, const SmallProblem* pr, int n, bool bf16, hipStream_t s) {
+  SmallArgs sa;
+  sa.problem[0] = pr[0];
+  sa.problem[1] = pr[n - 1];
+  sa.problems = n;
+  sa.tw = p->tw;
+  sa.B = (int)p->B;
+  sa.C = (int)p->C;
+  sa.Nf = (int)p->N;
+  sa.lg = ilog2(p->N);
+  sa.in_rows = (int)p->Nu;
+  sa.out_rows = (int)p->Nu;
+  sa.cc = p->small_cc;
+  sa.lcc = ilog2(p->small_cc);
+  sa.mz = 0xFFFFFFFFu / (uint32_t)(p->K * p->small_cc) + 1;
+  sa.mv = 0xFFFFFFFFu / (uint32_t)(p->K * p->small_cc / 2) + 1;
+  sa.groups = (int)((p->C + p->small_cc - 1) / p->small_cc);
+  // While every block has a CU of its own, the contraction waits for one
+  // lane's chain of operations: more lanes per point (parts) shorten it (L=6
+  // B=1 N=16 C=8 forward: 36 us with one part, 21 with two, 16 with four; L=4
+  // B=32 N=32 C=32: 24, 19).  With more blocks the lanes compete and one part
+  // is the fastest (L=2 B=512 N=16 C=8: 8.9, 9.7, 10.8).
+  const long long blocks = (long long)p->B * sa.groups * n;
+  sa.parts = 1;
+  if (blocks <= kSmallFewBlocks)
+    while (2 * sa.parts <= std::min(p->L <= 2 ? 2 : kSmallMaxParts, p->L + 1) &&
+           2 * sa.parts * p->small_lanes <= small_max_threads(p->L))
+      sa.parts *= 2;
+  sa.threads = sa.parts * p->small_lanes;
+  sa.bf16 = bf16;
+  return launch_small(p->L, sa, s);
+}
+
 // weights != nullptr: the channel-mixing stage with the unfused passes.
 // scales != nullptr (fp32 only): the adjoint form used by the backward,
 //   out = s_o * conv(s_a * q, s_b * reverse(k)), reverse(k)[n] = k[-n mod N],
@@ -343,7 +379,7 @@ int run_forward(cgconv_plan* p, const void* q, const void* k, void* out, bool bf
   const long long Nu = p->Nu;  // rows of q, k and out (padded rows are implicit zeros)
   const float inv_n = 1.0f / (float)N;
   hipEvent_t* ev = nullptr;  // events of this call if it is timed
-  const bool small = p->small && !mix && !scales;
+  const bool small = p->small_fwd && !mix && !scales;
   const int kind = mix ? 1 : (scales ? 2 : (small ? kKindSmall : 0));  // 2: one half of a backward
   if (p->timing_calls < p->timing_max && (p->timing_kind < 0 || p->timing_kind == kind)) {
     p->timing_kind = kind;
@@ -363,25 +399,8 @@ int run_forward(cgconv_plan* p, const void* q, const void* k, void* out, bool bf
   if (small) {
     // the whole convolution in one kernel: load, DFT, contraction, inverse
     // DFT and store per (batch element, channel group), spectra in LDS
-    SmallArgs sa;
-    sa.q = q;
-    sa.k = k;
-    sa.out = out;
-    sa.tw = p->tw;
-    sa.B = (int)p->B;
-    sa.C = (int)p->C;
-    sa.Nf = (int)N;
-    sa.lg = ilog2(N);
-    sa.in_rows = (int)Nu;
-    sa.out_rows = (int)Nu;
-    sa.cc = p->small_cc;
-    sa.lcc = ilog2(p->small_cc);
-    sa.mz = 0xFFFFFFFFu / (uint32_t)(K * p->small_cc) + 1;
-    sa.mv = 0xFFFFFFFFu / (uint32_t)(K * p->small_cc / 2) + 1;
-    sa.groups = (int)((p->C + p->small_cc - 1) / p->small_cc);
-    sa.threads = p->small_threads;
-    sa.bf16 = bf16;
-    e = launch_small(p->L, sa, s);
+    const SmallProblem pr{q, k, out, nullptr};
+    e = run_small(p, &pr, 1, bf16, s);
     if (e != hipSuccess) goto fail;
     mark();
   } else if (p->fused && !mix) {
@@ -736,27 +755,34 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
   }
   p->n_stages = (p->N1 && !p->fused) ? 5 : 3;
   p->n_stages_mix = p->N1 ? 5 : 3;
-  // DFT length <= 256: the one-block kernel, with the smallest channel group
-  // (a power of two, 2 .. 16) that gives a block at least 256 lanes (two per
-  // point), within the thread and LDS limits
+  // DFT length <= 256: the one-block kernel.  Channels per block: the fewest
+  // (a power of two, 2 .. 16) that leave at most 128 blocks, i.e. one block
+  // per CU also for the two gradients of a backward, or else the most that
+  // fit the thread and LDS limits (small blocks reread every cache line of a
+  // row once per channel group).
   const char* no_small = std::getenv("CGCONV_NO_SMALL");
   if (N <= kSmallMaxNf && L_max <= kSmallLmax && !p->force_generic && !(no_small && no_small[0] == '1')) {
-    const int64_t per_ch = 2 * (N / 2 + 1);  // lanes per channel
-    const int max_threads = small_max_threads(L_max);
+    auto lanes = [&](int c) { return (2 * (N / 2 + 1) * c + 63) / 64 * 64; };
+    auto fits = [&](int c) {
+      return lanes(c) <= small_max_threads(L_max) && small_lds_bytes(N, K, c) <= kSmallMaxLds;
+    };
     int cc = 2;
-    while (2 * cc <= 16 && cc < 2 * Cp && per_ch * cc < 256 && per_ch * 2 * cc <= max_threads &&
-           small_lds_bytes(N, K, 2 * cc) <= kSmallMaxLds)
-      cc *= 2;
-    const int64_t threads = (per_ch * cc + 63) / 64 * 64;
-    // a block reads cc of every C channels of a row: with fewer than a
-    // quarter, the loads touch so many more cache lines than they use that
-    // the three kernels, each reading whole rows, are faster (n-body size:
-    // one block 34 us, three kernels 28 us; tiny 10 against 14 us, molecule
-    // size 26 against 27 us)
-    if (threads <= max_threads && small_lds_bytes(N, K, cc) <= kSmallMaxLds && 4 * cc >= C) {
-      p->small = true;
+    while (2 * cc <= 16 && cc < 2 * Cp && batch * ((C + cc - 1) / cc) > 128 && fits(2 * cc)) cc *= 2;
+    if (fits(cc)) {
+      // Against the three kernels, whose loads read whole rows (us, forward
+      // one block / three kernels, then backward): at most one block per CU
+      // the one-block kernel wins (B=32 N=32 L=4 C=32 19 / 25, 23 / 53) but
+      // for long forward rows of which a block reads less than a quarter
+      // (B=16 N=256 L=3 C=16 32 / 26, 41 / 54; B=4 N=128 L=4 C=16 24 / 22,
+      // 27 / 48); with more blocks it wins where a block reads half a row, in
+      // the backward a quarter (B=256 N=32 L=3 C=32 at 16 channels 30 / 34,
+      // 66 / 68; B=128 N=64 L=4 C=16 at 4 41 / 38, 71 / 78; B=64 N=32 L=4
+      // C=64 at 8 40 / 36, B=64 N=64 L=3 C=64 at 8 39 / 34, 82 / 68).
+      const bool few = batch * ((C + cc - 1) / cc) <= kSmallFewBlocks;
+      p->small_fwd = few ? (N <= 64 || 4 * cc >= C) : 2 * cc >= C;
+      p->small_bwd = few || 4 * cc >= C;
       p->small_cc = cc;
-      p->small_threads = (int)threads;
+      p->small_lanes = (int)lanes(cc);
     }
   }
   hipError_t e = hipGetDevice(&p->device);
@@ -765,7 +791,7 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
     delete p;
     return nullptr;
   }
-  if (p->small && small_lds_bytes(N, K, p->small_cc) > 64 * 1024 &&
+  if ((p->small_fwd || p->small_bwd) && small_lds_bytes(N, K, p->small_cc) > 64 * 1024 &&
       (e = prepare_small(L_max, (int)small_lds_bytes(N, K, p->small_cc))) != hipSuccess) {
     set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e));
     delete p;
@@ -1332,6 +1358,27 @@ int cgconv_backward(cgconv_plan_t plan, const float* q, const float* k, const fl
     return CGCONV_ERR_INVALID_ARG;
   }
   const int K = plan->K;
+  if (plan->small_bwd) {
+    // both gradients in one launch of the one-block kernel
+    SmallProblem pr[2];
+    int n = 0;
+    if (grad_q) pr[n++] = {grad_out, k, grad_q, plan->d_bscale};
+    if (grad_k) pr[n++] = {grad_out, q, grad_k, plan->d_bscale + 3 * K};
+    hipEvent_t* ev = nullptr;
+    if (plan->timing_calls < plan->timing_max && (plan->timing_kind < 0 || plan->timing_kind == kKindSmall)) {
+      plan->timing_kind = kKindSmall;
+      ev = &plan->events[(size_t)plan->timing_calls * kMaxEvents];
+      ++plan->timing_calls;
+    }
+    if (ev) (void)hipEventRecord(ev[0], stream);
+    const hipError_t e = run_small(plan, pr, n, false, stream);
+    if (ev) (void)hipEventRecord(ev[1], stream);
+    if (e != hipSuccess) {
+      set_error("kernel launch failed: %s", hipGetErrorString(e));
+      return CGCONV_ERR_HIP;
+    }
+    return CGCONV_OK;
+  }
   if (grad_q) {
     const int st = run_forward(plan, grad_out, k, grad_q, false, stream, nullptr, plan->d_bscale);
     if (st != CGCONV_OK) return st;

@@ -545,8 +545,9 @@ void emit_path_split_body(FILE* f, int L, long* ops_out) {
 // each other, each lane takes the pairs {(l1,-a), (l2,a)} with l1 < l2 and
 // half the weight of the self-mirrored ones.  st.put(J, mu, acc) receives
 // both lanes' sums (mirror_out in cg_common.h turns them into the real-basis
-// outputs).  Per lane this is 1.04-1.1 times half the single-lane body's
-// operations, with 4 (L+1)(L+2)/2 input floats instead of 4 (L+1)^2.
+// outputs).  Per lane this is 1.08-1.1 times half the single-lane body's
+// operations at L_max 7 and 8 (1.12 at 6, 1.21 at 4), with 2 (L+1)(L+2) input
+// floats instead of 4 (L+1)^2.
 int hidx(int l, int m) { return l * (l + 1) / 2 + m; }
 std::string mqname(int l, int m) { return "q[" + std::to_string(hidx(l, m)) + "]"; }
 std::string mkname(int l, int m) { return "k[" + std::to_string(hidx(l, m)) + "]"; }
@@ -569,11 +570,13 @@ void emit_mirror_body(FILE* f, int L, long* ops_out) {
   L_cur = L;
   Emitter e{f, {}, 0};
   std::fprintf(f, "template <>\nstruct CgMirrorBody<%d> {\n  static constexpr int H = %d;\n", L, H);
-  std::fprintf(f, "  template <class Store>\n");
-  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&q)[%d], const float2 (&k)[%d], Store& st) {\n",
+  std::fprintf(f, "  // outputs M = +-MU\n  template <int MU, class Store>\n");
+  std::fprintf(f, "  static __device__ __forceinline__ void phase(const float2 (&q)[%d], const float2 (&k)[%d], Store& st) {\n",
                H, H);
+  std::vector<long> phase_ops;
   for (int mu = 0; mu <= L; ++mu) {
-    std::fprintf(f, "    {  // phase M = %d\n", mu);
+    const long ops0 = e.ops;
+    std::fprintf(f, "    if constexpr (MU == %d) {\n", mu);
     for (int J = mu; J <= L; ++J) std::fprintf(f, "      float2 %s;\n", acc_name(mu, J).c_str());
     for (int m1 = mu - L; 2 * m1 <= mu; ++m1) {
       const int m2 = mu - m1;
@@ -612,9 +615,20 @@ void emit_mirror_body(FILE* f, int L, long* ops_out) {
     e.inited.clear();
     std::fprintf(f, "      st.end_phase(%d);\n", mu);
     std::fprintf(f, "    }\n");
+    phase_ops.push_back(e.ops - ops0);
   }
   std::fprintf(f, "  }\n");
-  std::fprintf(f, "  static constexpr long kOps = %ld;  // VALU ops per lane (two lanes per point)\n};\n\n", e.ops);
+  // the phases of a bit mask (uniform over the wave)
+  std::fprintf(f, "  template <class Store>\n");
+  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&q)[%d], const float2 (&k)[%d], Store& st, unsigned phases = ~0u) {\n",
+               H, H);
+  for (int mu = 0; mu <= L; ++mu)
+    std::fprintf(f, "    if (phases & %uu) phase<%d>(q, k, st);\n", 1u << mu, mu);
+  std::fprintf(f, "  }\n");
+  std::fprintf(f, "  static constexpr long kOps = %ld;  // VALU ops per lane (two lanes per point)\n", e.ops);
+  std::fprintf(f, "  static constexpr int kPhaseOps[%d] = {", L + 1);
+  for (int mu = 0; mu <= L; ++mu) std::fprintf(f, "%s%ld", mu ? ", " : "", phase_ops[mu]);
+  std::fprintf(f, "};\n};\n\n");
   *ops_out = e.ops;
 }
 

@@ -170,24 +170,35 @@ hipError_t launch_cg_fused(const FusedArgs& a, hipStream_t s);
 // Whole convolution of one batch element and one channel group in one block
 // for DFT lengths Nf <= 256 (see cg_small.hip).  q, k: [B][in_rows][K][C],
 // out: [B][out_rows][K][C] (fp32, or bfloat16 bits when bf16); rows >=
-// in_rows are zero (zero-padded plans).  cc = 2^lcc channels per block (2 ..
-// 16), groups = ceil(C / cc) blocks per batch element, threads >= 2 * (Nf/2
-// + 1) * cc (one lane pair per point).  mz, mv: floor((2^32 - 1) / d) + 1
-// for d = K * cc and K * cc / 2 (divisions by multiply-high).
-struct SmallArgs {
+// in_rows are zero (zero-padded plans).  scales != nullptr: the adjoint form
+// out = s_o conv(s_a q, s_b reverse(k)) with per-component scales [s_a, s_b,
+// s_o][K].  cc = 2^lcc channels per block (2 .. 16), groups = ceil(C / cc)
+// blocks per batch element, problems (1 or 2) independent convolutions of one
+// launch; parts (1 .. 4) lane groups share a point's outputs, each of whole
+// waves and at least 2 * (Nf/2 + 1) * cc threads (one lane pair per point).
+// mz, mv: floor((2^32 - 1) / d) + 1 for d = K * cc and K * cc / 2 (divisions
+// by multiply-high).
+constexpr int kSmallMaxParts = 4;
+struct SmallProblem {
   const void* q;
   const void* k;
   void* out;
+  const float* scales;
+};
+struct SmallArgs {
+  SmallProblem problem[2];
   const float2* tw;  // exp(-2 pi i j / Nf), j < Nf
-  int B, C, Nf, lg, in_rows, out_rows, cc, lcc, groups, threads;
+  int B, C, Nf, lg, in_rows, out_rows, cc, lcc, groups, threads, parts, problems;
   uint32_t mz, mv;
+  uint32_t phases[kSmallMaxParts];  // bit mu: the part evaluates the outputs |M| = mu (set by the launcher)
   bool bf16;
 };
 constexpr int kSmallMaxNf = 256;
 constexpr int kSmallMaxLds = 80 * 1024;  // two blocks per CU
-// threads per block: three waves per SIMD up to L_max 4, two (the registers
+// threads per block: four waves per SIMD up to L_max 4, three (the registers
 // of the L_max 5, 6 lane pairs) above
-constexpr int small_max_threads(int L) { return L <= 4 ? 768 : 512; }
+constexpr int small_max_threads(int L) { return L <= 4 ? 1024 : 768; }
+constexpr int kSmallFewBlocks = 256;  // one block per CU
 constexpr int kSmallLmax = 6;
 template <int L>
 hipError_t launch_cg_small(const SmallArgs& a, hipStream_t s);
