@@ -266,7 +266,8 @@ def cpu_fft_baseline(q, k, L, budget_s, got):
 
 def dft_length(N, boundary):
     """Length of the token DFTs: N (cyclic) or the smallest power of two
-    >= 2N - 1 (zero-padded boundary)."""
+    >= 2N - 1 (zero-padded boundary; the library's length for the benchmark's
+    token counts, which are powers of two)."""
     if boundary == "cyclic":
         return N
     n = 2

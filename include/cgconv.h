@@ -101,8 +101,8 @@ enum cgconv_boundary {
  *   out[b,i,(J,M),c] = sum_paths sum R^{(l1 l2 J)}[M,m1,m2]
  *                      * sum_{j=0}^{i} q[b,j,(l1,m1),c] * k[b,i-j,(l2,m2),c]
  *
- * computed exactly by DFTs of length Nf = the smallest power of two >= 2N-1
- * over the zero-padded tokens (no term wraps around).  With the linear
+ * computed exactly by DFTs of a length Nf >= 2N-1 over the zero-padded tokens
+ * (no term wraps around; Nf is a power of two or 3, 5 or 7 times one).  With the linear
  * boundary N may be any value 1 <= N <= CGCONV_NMAX/2 (not only a power of
  * two); q, k, out keep N rows, and the workspace is sized for Nf rows.
  * Every entry point taking a plan follows its boundary: cgconv_forward,

@@ -61,6 +61,8 @@ def build(jobs: int | None = None, verbose: bool = True) -> str:
         ([HIPCC, "-c"] + HIP_FLAGS, "cg.hip", "cg.o", []),
         ([HIPCC, "-c"] + HIP_FLAGS, "gft.hip", "gft.o", []),
     ]
+    for P in (3, 5, 7):
+        units.append(([HIPCC, "-c"] + HIP_FLAGS, "fft_odd.hip", "fft_odd_P%d.o" % P, ["-DCGCONV_TU_P=%d" % P]))
     for L in range(LGEN, -1, -1):  # largest first: it compiles longest
         units.append(([HIPCC, "-c"] + HIP_FLAGS, "cg_gen.hip", "cg_gen_L%d.o" % L,
                       ["-DCGCONV_TU_L=%d" % L, '-DCGCONV_BODY="cg_body_L%d.inc"' % L]))

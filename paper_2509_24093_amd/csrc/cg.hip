@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kGenThreads) void cg_generic_kernel(CgArgs a) {
   const Point pt = point_of(p, a);
   {
     const bool cv = pt.valid && pt.c < a.C;
-    const long long wn = (a.N - pt.w) & (a.N - 1);
+    const long long wn = pt.w ? a.N - pt.w : 0;
     const float2* za = a.Z + ((pt.b * a.N + freq_row(pt.w, a)) * K) * a.C + pt.c;
     const float2* zb = a.Z + ((pt.b * a.N + freq_row(wn, a)) * K) * a.C + pt.c;
     for (int k = 0; k < K; ++k) {

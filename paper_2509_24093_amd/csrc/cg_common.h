@@ -119,7 +119,7 @@ struct Point {
 
 // storage row of frequency w (see CgArgs)
 __device__ __forceinline__ long long freq_row(long long w, const CgArgs& a) {
-  return ((w & ((1LL << a.n1_log2) - 1)) << a.n2_log2) | (w >> a.n1_log2);
+  return a.rows.row((int)w);
 }
 
 __device__ __forceinline__ Point point_of(long long p, const CgArgs& a) {
@@ -159,7 +159,7 @@ __device__ __forceinline__ void to_complex_basis(Arr& qa, Arr& ka) {
 template <int K, class Arr>
 __device__ __forceinline__ void load_unpack(const CgArgs& a, const Point& pt, Arr& qa, Arr& ka) {
   const bool cv = pt.valid && pt.c < a.C;
-  const long long wn = (a.N - pt.w) & (a.N - 1);
+  const long long wn = pt.w ? a.N - pt.w : 0;
   const int cl = pt.c < a.C ? pt.c : a.C - 1;  // the padding channel of odd C loads a real one, then zeroes it
   const float2* za = a.Z + ((pt.b * a.N + freq_row(pt.w, a)) * K) * a.C + cl;
   const float2* zb = a.Z + ((pt.b * a.N + freq_row(wn, a)) * K) * a.C + cl;
@@ -256,7 +256,7 @@ struct SplitPairStore {
 template <int K, int G = 16, class Arr>
 __device__ __forceinline__ void load_unpack_half(const CgArgs& a, const Point& pt, int half, Arr& x) {
   const bool cv = pt.valid && pt.c < a.C;
-  const long long wn = (a.N - pt.w) & (a.N - 1);
+  const long long wn = pt.w ? a.N - pt.w : 0;
   const int cl = pt.c < a.C ? pt.c : a.C - 1;
   const float2* z = a.Z + ((pt.b * a.N + freq_row(half ? wn : pt.w, a)) * K) * a.C + cl;
   // (groups of 8 with two or three in flight, or of 16 or 32 with one or
@@ -314,7 +314,7 @@ template <int L, int G = 8, class Arr>
 __device__ __forceinline__ void load_unpack_mirror(const CgArgs& a, const Point& pt, int half, float g, Arr& q, Arr& k) {
   constexpr int K = (L + 1) * (L + 1), H = (L + 1) * (L + 2) / 2;
   const bool cv = pt.valid && pt.c < a.C;
-  const long long wn = (a.N - pt.w) & (a.N - 1);
+  const long long wn = pt.w ? a.N - pt.w : 0;
   const int cl = pt.c < a.C ? pt.c : a.C - 1;
   const float2* z = a.Z + ((pt.b * a.N + freq_row(half ? wn : pt.w, a)) * K) * a.C + cl;
   constexpr int D = 1, NG = (H + G - 1) / G;
@@ -367,7 +367,7 @@ __device__ __forceinline__ void load_unpack_mirror(const CgArgs& a, const Point&
 
 __device__ __forceinline__ SplitPairStore make_split_store(const CgArgs& a, const Point& pt, int half, float g, int K) {
   SplitPairStore st;
-  const long long wn = (a.N - pt.w) & (a.N - 1);
+  const long long wn = pt.w ? a.N - pt.w : 0;
   st.Cp = a.Cp;
   st.g = g;
   st.even = (pt.c & 1) == 0;
@@ -381,7 +381,7 @@ __device__ __forceinline__ SplitPairStore make_split_store(const CgArgs& a, cons
 
 __device__ __forceinline__ PairStore make_store(const CgArgs& a, const Point& pt, int K) {
   PairStore st;
-  const long long wn = (a.N - pt.w) & (a.N - 1);
+  const long long wn = pt.w ? a.N - pt.w : 0;
   st.Cp = a.Cp;
   st.even = (pt.c & 1) == 0;
   const bool write = pt.valid && (st.even || (wn != pt.w));

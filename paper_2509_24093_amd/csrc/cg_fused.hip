@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreadsF, 2) void cg_fused_kernel(FusedArgs a) {
   const int b = unit / a.units, w1 = unit % a.units;
   const int N1 = a.N1;
   const long long N = a.N;
-  const int w1b = (N1 - w1) & (N1 - 1);
+  const int w1b = w1 ? N1 - w1 : 0;
   const bool selfpaired = w1b == w1;
   const int tid = threadIdx.x;
   const int p = tid >> 2, cc = tid & 3;
@@ -178,8 +178,7 @@ __global__ __launch_bounds__(kThreadsF, 2) void cg_fused_kernel(FusedArgs a) {
   }
   if (tid < 2 * kN2) {
     const int cls = tid / kN2, n2 = tid % kN2;
-    const long long e = ((long long)n2 * (cls ? w1b : w1)) & (N - 1);
-    twpv = a.tw[e];  // conjugated when written (no use of the value before then)
+    twpv = a.tw[n2 * (cls ? w1b : w1)];  // index < 64 N1 = N; conjugated when written (no use of the value before then)
   }
 
   float2 qa[K], ka[K];
@@ -314,7 +313,8 @@ __global__ __launch_bounds__(kThreadsF, 2) void cg_fused_kernel(FusedArgs a) {
 
 template <>
 hipError_t launch_cg_fused<CGCONV_TU_L>(const FusedArgs& a, hipStream_t s) {
-  if (a.N1 < 2 || a.N != (long long)a.N1 * kN2 || a.Cb != (a.C + kCc - 1) / kCc) return hipErrorInvalidValue;
+  // class pairs {w1, N1 - w1} need an even N1
+  if (a.N1 < 2 || (a.N1 & 1) || a.N != (long long)a.N1 * kN2 || a.Cb != (a.C + kCc - 1) / kCc) return hipErrorInvalidValue;
   // per-batch-element byte offsets of Y are 32-bit
   if ((long double)a.N * Geo<CGCONV_TU_L>::K * a.C * 8 >= 4294967296.0L) return hipErrorInvalidValue;
   const long long units = (long long)a.B * a.units;

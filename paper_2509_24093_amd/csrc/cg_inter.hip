@@ -82,12 +82,13 @@ struct InterStore {
   const float* Wl;  // LDS [L+1][kWRows][kSlots]: the head's matrices (rows o >= kWRows of the MFMA operand are zero)
   char* Wb;         // packed output spectra of this batch element (bytes)
   long long N;
-  int n1_log2, n2_log2, F, w0, Cpo, co0, mo;
+  RowMap rows;
+  int F, w0, Cpo, co0, mo;
   int slot, pt, lane, wave;
 
   // storage row of frequency w (rows as in the unfused CG stage)
   __device__ __forceinline__ long long row_of(long long w) const {
-    return ((w & ((1LL << n1_log2) - 1)) << n2_log2) | (w >> n1_log2);
+    return rows.row((int)w);
   }
 
   // component kout = J^2 + J + M of phase mu = |M|: slot ci within the
@@ -121,7 +122,7 @@ struct InterStore {
       float other[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) other[i] = swap_pair(acc[i]);
-      const long long wn = (N - w) & (N - 1);
+      const long long wn = w ? N - w : 0;
       const bool store = has && w < F && !(ri == 1 && wn == w);  // one row for w = 0, N/2
       if (!store) continue;
       const int kout = J * J + J + (sgn ? -mu : mu);
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kThreadsI, 3) void cg_inter_kernel(InterArgs a) {
                   : 0.f;
   }
   auto rowp = [&](long long x) {
-    return ((x & ((1LL << a.n1_log2) - 1)) << a.n2_log2) | (x >> a.n1_log2);
+    return (long long)a.rows.row((int)x);
   };
   // the head's spectra at w and N - w of the block's points, loaded once
   // per block (64 contiguous bytes per row and component), four loads per
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(kThreadsI, 3) void cg_inter_kernel(InterArgs a) {
                   pl = idx / (2 * kInterMmax * K);
         const long long wp = (long long)g * kPts + pl;
         const long long wv = wp < a.F ? wp : 0;
-        const long long row = rowp(side ? (a.N - wv) & (a.N - 1) : wv);
+        const long long row = rowp(side && wv ? a.N - wv : wv);
         v[u] = (idx < ZE && ch < a.m) ? Zb[(row * K + k) * a.C + ch] : make_float2(0.f, 0.f);
       }
 #pragma unroll
@@ -246,8 +247,7 @@ __global__ __launch_bounds__(kThreadsI, 3) void cg_inter_kernel(InterArgs a) {
   st.Wl = sW;
   st.Wb = reinterpret_cast<char*>(a.W + (long long)b * a.N * K * a.Cpo);
   st.N = a.N;
-  st.n1_log2 = a.n1_log2;
-  st.n2_log2 = a.n2_log2;
+  st.rows = a.rows;
   st.F = a.F;
   st.w0 = g * kPts;
   st.Cpo = a.Cpo;

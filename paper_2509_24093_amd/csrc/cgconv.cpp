@@ -55,6 +55,27 @@ int ilog2(int64_t x) {
   return r;
 }
 
+// DFT length of a zero-padded plan of N tokens: the smallest of 2^a, 3 * 2^a,
+// 5 * 2^a (from 640) and 7 * 2^a (from 3584) that is >= 2N - 1.  They are 64 *
+// N1 or 128 * N1 with the odd factor in N1 <= 448, the length of the outer
+// passes.  Every stage's time goes with the length; measured against the next
+// power of two (forward, us, B=4 L=5 C=20): 640 62 / 66, 1280 68 / 83, 3072
+// 131 / 140, 5120 174 / 255, 10240 345 / 511, 12288 397 / 512, 20480 727 /
+// 1019, 49152 2052 / 2424.  The radix-7 passes give 2-10% from 3584 on (140 /
+// 144, 7168 237 / 260, 57344 2383 / 2441) and lose below (1792 89 / 84).
+int64_t linear_dft_length(int64_t N) {
+  const int64_t need = 2 * N - 1;
+  int64_t best = 2;
+  while (best < need) best *= 2;
+  const int64_t first[3][2] = {{3, 768}, {5, 640}, {7, 3584}};
+  for (const auto& f : first) {
+    int64_t len = f[1];
+    while (len < need) len *= 2;
+    if (need > 512 && len < best) best = len;
+  }
+  return best;
+}
+
 }  // namespace
 
 struct cgconv_plan {
@@ -277,7 +298,7 @@ PassArgs base_args(const cgconv_plan* p) {
   a.C = (int)p->C;
   a.Cp = (int)p->Cp;
   a.KC = (int)(p->K * p->C);
-  a.Nmask = (int)(p->N - 1);
+  a.N = (int)p->N;
   a.scale = 1.0f;
   a.in_rows = (int)p->Nu;
   a.out_rows = (int)p->Nu;
@@ -373,8 +394,7 @@ int run_forward(cgconv_plan* p, const void* q, const void* k, void* out, bool bf
   ca.tkey = p->d_tkey;
   ca.tcoef = p->d_tcoef;
   ca.wmix = p->d_wmix;
-  ca.n1_log2 = ilog2(p->N1 ? p->N1 : p->N);
-  ca.n2_log2 = ilog2(p->N1 ? p->N2 : 1);
+  ca.rows = p->N1 ? make_row_map(p->N1, p->N2) : make_row_map(p->N, 1);
   const long long N = p->N;
   const long long Nu = p->Nu;  // rows of q, k and out (padded rows are implicit zeros)
   const float inv_n = 1.0f / (float)N;
@@ -546,8 +566,7 @@ int run_interchannel(cgconv_plan* p, int heads, int mo, const float* q, const fl
     mark();
     ia.Z = p->ws1;
     ia.W = p->ws2;
-    ia.n1_log2 = ilog2(N);
-    ia.n2_log2 = 0;
+    ia.rows = make_row_map(N, 1);
     if ((e = launch_inter(p->L, ia, s)) != hipSuccess) goto fail;
     mark();
     if ((e = pass((int)N, IN_COMPLEX, OUT_SPLIT_F32, 1, 1, p->ws2, nullptr, out, N * Wo, Nu * K * Co, (int)Wo, 0, 1,
@@ -566,8 +585,7 @@ int run_interchannel(cgconv_plan* p, int heads, int mo, const float* q, const fl
     mark();
     ia.Z = p->ws2;
     ia.W = p->ws1;
-    ia.n1_log2 = ilog2(N1);
-    ia.n2_log2 = ilog2(N2);
+    ia.rows = make_row_map(N1, N2);
     if ((e = launch_inter(p->L, ia, s)) != hipSuccess) goto fail;
     mark();
     if ((e = pass(N2, IN_COMPLEX, OUT_COMPLEX, 1, N1, p->ws1, nullptr, p->ws2, N * Wo, N * Wo, (int)Wo, N2, 1, N2, 1,
@@ -700,16 +718,15 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
     set_error("invalid L_max=%d", L_max);
     return nullptr;
   }
-  // DFT length: N itself (cyclic), or the smallest power of two >= 2N - 1 so
-  // that no term of the zero-padded sum wraps around (linear)
+  // DFT length: N itself (cyclic), or a length >= 2N - 1 so that no term of
+  // the zero-padded sum wraps around (linear): see linear_dft_length
   int64_t N = N_tokens;
   if (linear) {
     if (N_tokens > CGCONV_NMAX / 2) {
       set_error("unsupported N=%lld: the linear boundary needs N <= %d", (long long)N_tokens, CGCONV_NMAX / 2);
       return nullptr;
     }
-    N = 2;
-    while (N < 2 * N_tokens - 1) N *= 2;
+    N = linear_dft_length(N_tokens);
   } else if (!is_pow2(N) || N > CGCONV_NMAX) {
     set_error("unsupported N=%lld: need a power of two <= %d", (long long)N, CGCONV_NMAX);
     return nullptr;
@@ -748,6 +765,9 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
     p->fused = true;
     p->N2 = 64;
     p->N1 = N / 64;
+  } else if (!is_pow2(N)) {
+    p->N2 = N <= 64 * 448 ? 64 : 128;  // the odd factor goes to the outer passes, N1 <= 448
+    p->N1 = N / p->N2;
   } else if (N > 256) {
     const int lg = ilog2(N);
     p->N1 = int64_t(1) << ((lg + 1) / 2);

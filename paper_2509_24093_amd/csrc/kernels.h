@@ -47,7 +47,7 @@ struct PassArgs {
   int KC;                // scalars per row of the split output: K*C
   int gs_in, es_in, gs_out, fs_out;
   int tw_stride;         // N / R
-  int Nmask;             // N - 1
+  int N;                 // length of the token DFT
   int inter;             // 1: apply the inter-pass twiddle
   float scale;
   const float* in_scale;  // IN_PAIR_F32_SCALED_REV: [2][K] per-component input scales
@@ -57,7 +57,7 @@ struct PassArgs {
 };
 
 struct PassDesc {
-  int R;        // DFT length, power of two, 2..256
+  int R;        // DFT length: a power of two, 2..512, or 3, 5 or 7 times one, 10..448
   int in_mode;  // InMode
   int out_mode; // OutMode
   int dir;      // -1 forward, +1 inverse
@@ -67,19 +67,39 @@ struct PassDesc {
 };
 
 hipError_t launch_fft_pass(const PassDesc& d, hipStream_t s);
+// passes of R = P * 2^j (zero-padded plans), built once per P = 3, 5, 7
+template <int P>
+hipError_t launch_fft_pass_odd(const PassDesc& d, hipStream_t s);
+
+// Storage row of frequency w = w1 + n1 w2 (w1 < n1): w1 n2 + w2.  n1 need not
+// be a power of two; the division is a multiply-high by magic =
+// floor((2^32 - 1) / n1) + 1, exact for w * n1 < 2^32 (n1 >= 2).
+struct RowMap {
+  int n1, n2;
+  uint32_t magic;
+#ifdef __HIPCC__
+  __device__ __forceinline__ int row(int w) const {
+    const int w2 = (int)__umulhi((uint32_t)w, magic);
+    return (w - w2 * n1) * n2 + w2;
+  }
+#endif
+};
+inline RowMap make_row_map(long long n1, long long n2) {
+  return {(int)n1, (int)n2, 0xFFFFFFFFu / (uint32_t)n1 + 1};
+}
 
 // Frequency-domain CG stage.  Z: full spectra of z = q + i k, [B][N][K][C]
 // float2.  W: spectra of out_c + i out_{c+1} (channel pairs), [B][N][K][Cp]
 // float2.  Every frequency pair (w, N-w), w = 0..N/2, is one point per channel.
-// Frequency w is stored at row pos(w) = (w mod N1) * N2 + w / N1 of Z and W
-// (N1 = N, N2 = 1 for single-pass transforms), so that the DFT passes on
-// either side of this stage read and write contiguous row blocks.
+// Frequency w is stored at row (w mod N1) * N2 + w / N1 of Z and W (RowMap; N1
+// = N, N2 = 1 for single-pass transforms), so that the DFT passes on either
+// side of this stage read and write contiguous row blocks.
 struct CgArgs {
   const float2* Z;
   float2* W;
   float2* trash;    // K*Cp float2 after the real data of W: target of masked stores
   long long N;
-  int n1_log2, n2_log2;
+  RowMap rows;
   long long F;      // N/2 + 1
   int K, C, Cp;
   long long npts;   // B * F * 2Cp
@@ -123,7 +143,7 @@ struct InterArgs {
   float2* W;        // packed output spectra [B][N][K][Cpo]
   const float* wt;  // [H][L+1][mo][m*m]
   long long N;
-  int n1_log2, n2_log2;
+  RowMap rows;
   int F;            // N/2 + 1
   int B, C, H, m, mo, Cpo;
 };
