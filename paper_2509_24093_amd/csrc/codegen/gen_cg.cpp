@@ -113,7 +113,7 @@ struct Emitter {
 using TermMap = std::map<std::array<int, 4>, std::vector<Term>>;  // (l1, m1, l2, m2) -> terms
 
 std::string qname(int l, int m) { return "qa[" + std::to_string(comp(l, m)) + "]"; }
-std::string kname(int l, int m) { return "kb[" + std::to_string(comp(l, m)) + "]"; }
+std::string kname(int l, int m) { return "ka[" + std::to_string(comp(l, m)) + "]"; }
 
 // Cheaper of product and key form for one half (fixed factor f1 of the l1
 // side, varying factor of the l2 side) with the given (l2 -> terms) lists.
@@ -298,11 +298,9 @@ void emit_body(FILE* f, int L, long* ops_out) {
 
   Emitter e{f, {}, 0};
   std::fprintf(f, "template <>\nstruct CgBody<%d> {\n  static constexpr int K = %d;\n", L, K);
-  // ka: an array of K float2, or an accessor whose operator[] returns the
-  // component by value (a kernel whose lanes share key spectra reads them
-  // from LDS)
-  std::fprintf(f, "  template <class Store, class KA>\n");
-  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&qa)[%d], const KA& ka, Store& st) {\n", K);
+  std::fprintf(f, "  template <class Store>\n");
+  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&qa)[%d], const float2 (&ka)[%d], Store& st) {\n", K,
+               K);
   for (int mu = 0; mu <= L; ++mu) {
     std::fprintf(f, "    {  // phase |M| = %d\n", mu);
     std::vector<int> Ms = mu == 0 ? std::vector<int>{0} : std::vector<int>{mu, -mu};
@@ -313,11 +311,9 @@ void emit_body(FILE* f, int L, long* ops_out) {
         const int m2 = M - m1;
         if (m2 < -L || m2 > L || m1 > m2) continue;
         std::fprintf(f, "      // blocks m1=%d m2=%d and swapped\n", m1, m2);
-        std::fprintf(f, "      {\n      const auto& kb = cg_kfence(ka);\n");
         for (int l1 = std::abs(m1); l1 <= L; ++l1)
           emit_row(e, terms_of, M, l1, m1, m2,
                    {qname(l1, m1), kname(l1, m1), qname, kname, [](int, int) { return 1.0; }});
-        std::fprintf(f, "      }\n");
       }
     }
     // output transform and stores
@@ -632,6 +628,202 @@ void emit_mirror_body(FILE* f, int L, long* ops_out) {
   *ops_out = e.ops;
 }
 
+// Contraction of every channel pair of a head (CgPairsBody<L>::run), one
+// point per wave: for 8 query channels c1 and 8 key channels c2,
+//   w[J,M](c1, c2) = sum_x t[J,M,x](c2) q[x](c1),  x = (l1, m1),
+//   t[J,M,x](c2) = sum_l2 coef k[l2, M - m1](c2).
+// t depends on the key channel only, so its coefficients are applied once per
+// key channel instead of once per pair, and the second sum is an outer
+// product of t (rows) and q (columns): v_mfma_f32_4x4x1 (16 blocks), block b =
+// lanes 4b .. 4b+3.  Block 2 c2 + h holds the columns c1 = 4h + (lane & 3);
+// its four rows are the real and imaginary parts of t of two output degrees,
+// row r = part (r & 1) of degree Ja + (r >> 1), computed by lane 4b + r from
+// its own part kp of the key components.  The two blocks of a key channel
+// compute t for two different x (l1 and l1 + 1) and broadcast them to each
+// other (cbsz = 1).  All coefficients are real: the factor i of the terms with
+// l1 + l2 + J odd is i^J i^l1 i^l2 (parities) times a sign, so kp and q carry
+// i^l and the outputs i^J.  The lane-dependent coefficients (two degrees, two
+// x) come from a table of 4-slot entries [entry][2 h + (r >> 1)][4].
+// At L_max = 6: 2424 matrix instructions (four FMAs per lane each) and 2.2k
+// FMAs per wave, against 18.9k operations of one pair per lane.
+struct PairsTable {
+  std::vector<std::array<float, 4>> slots;  // [slot][2 h + row degree]
+};
+constexpr size_t kPairsSlots = 16;  // slots of one pipeline stage
+
+void emit_pairs_body(FILE* f, int L, long* ops_out, long* mfma_out) {
+  const int K = (L + 1) * (L + 1);
+  std::vector<Term> terms = contraction_terms(L);
+  std::map<std::array<int, 5>, const Term*> at;  // (l1, m1, l2, m2, J)
+  for (const Term& t : terms) at[{t.l1, t.m1, t.l2, t.m2, t.J}] = &t;
+  auto coef = [&](int l1, int m1, int l2, int m2, int J) {
+    auto it = at.find({l1, m1, l2, m2, J});
+    if (it == at.end()) return 0.0;
+    const int a = J & 1, p1 = l1 & 1, p2 = l2 & 1, b = p1 ^ p2;
+    if (it->second->imag != ((a ^ b) != 0)) {
+      std::fprintf(stderr, "gen_cg: parity of a pair term (%d %d %d %d J=%d)\n", l1, m1, l2, m2, J);
+      std::exit(1);
+    }
+    return it->second->coef * ((a & b) ? -1.0 : 1.0) * ((p1 & p2) ? -1.0 : 1.0);
+  };
+  PairsTable tab;
+  long ops = 0, mfmas = 0;
+  std::fprintf(f, "template <>\nstruct CgPairsBody<%d> {\n  static constexpr int K = %d;\n", L, K);
+  std::fprintf(f, "  template <class Tab, class Store>\n");
+  std::fprintf(f, "  static __device__ __forceinline__ void run(const float2 (&q)[%d], const float (&kp)[%d], Tab tab, Store& st) {\n",
+               K, K);
+  for (int mu = 0; mu <= L; ++mu) {
+    std::fprintf(f, "    {  // phase |M| = %d\n", mu);
+    const int nj = L + 1 - mu, ng = (nj + 1) / 2;
+    const std::vector<int> Ms = mu == 0 ? std::vector<int>{0} : std::vector<int>{mu, -mu};
+    for (int M : Ms)
+      for (int J = mu; J <= L; ++J) std::fprintf(f, "      float2 %s;\n", acc_name(M, J).c_str());
+    for (int M : Ms) {
+      std::fprintf(f, "      {\n");
+      for (int g = 0; g < ng; ++g) std::fprintf(f, "      v4f dr%d = {0.f, 0.f, 0.f, 0.f}, di%d = {0.f, 0.f, 0.f, 0.f};\n", g, g);
+      // one t of every unit (m1, l1, l1 + 1, group): its slots and outer products
+      struct Unit {
+        int g, m1, l1;
+        std::vector<int> k;  // key components of the slots
+        std::vector<std::array<float, 4>> c;
+        bool any[2] = {false, false};
+      };
+      std::vector<Unit> units;
+      for (int m1 = std::max(-L, M - L); m1 <= std::min(L, M + L); ++m1) {
+        const int m2 = M - m1;
+        for (int l1 = std::abs(m1); l1 <= L; l1 += 2) {
+          for (int g = 0; g < ng; ++g) {
+            const int Ja = mu + 2 * g;
+            Unit u;
+            u.g = g;
+            u.m1 = m1;
+            u.l1 = l1;
+            for (int l2 = std::abs(m2); l2 <= L; ++l2) {
+              std::array<float, 4> c;
+              bool any = false;
+              for (int h = 0; h < 2; ++h)
+                for (int d = 0; d < 2; ++d) {
+                  const bool in = l1 + h <= L && Ja + d <= L;
+                  c[2 * h + d] = in ? (float)coef(l1 + h, m1, l2, m2, Ja + d) : 0.f;
+                  if (c[2 * h + d] != 0.f) any = u.any[h] = true;
+                }
+              if (!any) continue;
+              u.k.push_back(comp(l2, m2));
+              u.c.push_back(c);
+            }
+            if (!u.k.empty()) units.push_back(u);
+          }
+        }
+      }
+      // stages of consecutive units with at most kPairsSlots slots
+      std::vector<std::vector<int>> stages;
+      size_t left = 0;
+      for (size_t i = 0; i < units.size(); ++i) {
+        if (units[i].k.size() > left) {
+          stages.push_back({});
+          left = kPairsSlots;
+        }
+        stages.back().push_back((int)i);
+        left -= units[i].k.size();
+      }
+      std::vector<size_t> first;  // first table entry of each stage, and the end
+      std::vector<std::vector<std::pair<int, int>>> order;  // (unit, slot of the unit), the chains side by side
+      for (auto& st : stages) {
+        first.push_back(tab.slots.size() / 4);
+        order.push_back({});
+        for (size_t i = 0;; ++i) {
+          bool more = false;
+          for (int u : st)
+            if (i < units[u].k.size()) {
+              tab.slots.push_back(units[u].c[i]);
+              order.back().push_back({u, (int)i});
+              more = true;
+            }
+          if (!more) break;
+        }
+        while (tab.slots.size() % 4) tab.slots.push_back({0.f, 0.f, 0.f, 0.f});
+      }
+      first.push_back(tab.slots.size() / 4);
+      // Software pipeline, kept by scheduling barriers: step s loads the
+      // coefficients of stage s, computes the t of stage s - 1 and runs the
+      // outer products of stage s - 2, so that no instruction waits for the
+      // one before it.
+      for (auto& st : stages)
+        for (int u : st) std::fprintf(f, "      float t%d;\n", u);
+      for (size_t e = first.front(); e < first.back(); ++e) std::fprintf(f, "      v4f c%zu;\n", e);
+      const int ns = (int)stages.size();
+      for (int step = 0; step < ns + 2; ++step) {
+        if (step < ns) {
+          std::fprintf(f, "      { const auto tb = tab.fresh();\n");
+          for (size_t e = first[step]; e < first[step + 1]; ++e) std::fprintf(f, "      c%zu = tb.at(%zu);\n", e, e);
+          std::fprintf(f, "      }\n");
+        }
+        if (step >= 1 && step - 1 < ns) {
+          const size_t s0 = 4 * first[step - 1];
+          for (size_t i = 0; i < order[step - 1].size(); ++i) {
+            const int u = order[step - 1][i].first, j = order[step - 1][i].second;
+            const size_t slot = s0 + i;
+            if (j == 0)
+              std::fprintf(f, "      t%d = c%zu[%zu] * kp[%d];\n", u, slot / 4, slot % 4, units[u].k[j]);
+            else
+              std::fprintf(f, "      t%d = fmaf(c%zu[%zu], kp[%d], t%d);\n", u, slot / 4, slot % 4, units[u].k[j], u);
+            ++ops;
+          }
+        }
+        if (step >= 2) {
+          for (int h = 0; h < 2; ++h)
+            for (int u : stages[step - 2]) {
+              if (!units[u].any[h]) continue;
+              const int x = comp(units[u].l1 + h, units[u].m1), g = units[u].g;
+              std::fprintf(f, "      dr%d = __builtin_amdgcn_mfma_f32_4x4x1f32(t%d, q[%d].x, dr%d, 1, %d, 0);\n", g, u, x, g, h);
+              std::fprintf(f, "      di%d = __builtin_amdgcn_mfma_f32_4x4x1f32(t%d, q[%d].y, di%d, 1, %d, 0);\n", g, u, x, g, h);
+              mfmas += 2;
+            }
+        }
+        std::fprintf(f, "      __builtin_amdgcn_sched_barrier(0);\n");
+      }
+      // w = i^J ((dr[re] - di[im]) + i (di[re] + dr[im]))
+      for (int J = mu; J <= L; ++J) {
+        const int g = (J - mu) / 2, r = 2 * ((J - mu) & 1);
+        char re[64], im[64];
+        std::snprintf(re, sizeof re, "dr%d[%d] - di%d[%d]", g, r, g, r + 1);
+        std::snprintf(im, sizeof im, "di%d[%d] + dr%d[%d]", g, r, g, r + 1);
+        if (J & 1)
+          std::fprintf(f, "      %s = make_float2(-(%s), %s);\n", acc_name(M, J).c_str(), im, re);
+        else
+          std::fprintf(f, "      %s = make_float2(%s, %s);\n", acc_name(M, J).c_str(), re, im);
+        ops += 2;
+      }
+      std::fprintf(f, "      }\n");
+    }
+    for (int J = mu; J <= L; ++J) {
+      if (mu == 0) {
+        std::fprintf(f, "      st(%d, %s);\n", comp(J, 0), acc_name(0, J).c_str());
+      } else {
+        const std::string p = acc_name(mu, J), m = acc_name(-mu, J);
+        std::fprintf(f, "      st(%d, make_float2(%s.x + %s.x, %s.y + %s.y));\n", comp(J, mu), m.c_str(), p.c_str(),
+                     m.c_str(), p.c_str());
+        std::fprintf(f, "      st(%d, make_float2(%s.y - %s.y, %s.x - %s.x));\n", comp(J, -mu), m.c_str(), p.c_str(),
+                     p.c_str(), m.c_str());
+        ops += 4;
+      }
+    }
+    std::fprintf(f, "      st.end_phase(%d);\n    }\n", mu);
+  }
+  while (tab.slots.size() % 4) tab.slots.push_back({0.f, 0.f, 0.f, 0.f});
+  std::fprintf(f, "  }\n  static constexpr int kEntries = %zu;  // table entries of 16 floats\n", tab.slots.size() / 4);
+  std::fprintf(f, "  static __device__ const float* table();\n};\n");
+  std::fprintf(f, "static __device__ __attribute__((aligned(16))) const float pairs_table_L%d[%zu] = {\n", L, tab.slots.size() * 4);
+  for (size_t e = 0; e < tab.slots.size() / 4; ++e) {
+    for (int sel = 0; sel < 4; ++sel)
+      for (int i = 0; i < 4; ++i) std::fprintf(f, "%.9ef, ", (double)tab.slots[4 * e + i][sel]);
+    std::fprintf(f, "\n");
+  }
+  std::fprintf(f, "};\ninline __device__ const float* CgPairsBody<%d>::table() { return pairs_table_L%d; }\n\n", L, L);
+  *ops_out = ops;
+  *mfma_out = mfmas;
+}
+
 // Token-wise real-basis product for the value tensor product (CgRealBody<L>::run):
 //   f[J,M] = sum R^{(l1 l2 J)}[M,m1,m2] a[l1,m1] b[l2,m2]   (a, b, f real)
 // from the real-basis table.  The two ordered terms of a component pair
@@ -729,7 +921,12 @@ int main(int argc, char** argv) {
     emit_real_body(f, L, &rops);
     emit_mirror_body(f, L, &sops);
     emit_path_split_body(f, L, &psops);
+    long pops = 0, pmfma = 0;
+    std::fprintf(f, "#ifdef CGCONV_PAIRS_BODY  // the inter-channel kernel only\n");
+    emit_pairs_body(f, L, &pops, &pmfma);
+    std::fprintf(f, "#endif\n");
     std::fclose(f);
+    std::fprintf(stderr, "gen_cg: L=%d channel-pairs body: %ld ops and %ld matrix instructions per wave\n", L, pops, pmfma);
     std::fprintf(stderr,
                  "gen_cg: L=%d ops/point=%ld real token-wise ops=%ld mirror lane-pair ops/lane=%ld "
                  "per-path lane-pair ops/lane=%ld\n",

@@ -146,6 +146,7 @@ struct InterArgs {
   RowMap rows;
   int F;            // N/2 + 1
   int B, C, H, m, mo, Cpo;
+  int loop;         // groups of points per block (set by the launcher)
 };
 template <int L>
 hipError_t launch_cg_inter(const InterArgs& a, hipStream_t s);

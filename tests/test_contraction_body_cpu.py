@@ -40,7 +40,6 @@ static inline V sw(V v) { return V(v.b, v.a); }
 static inline V lane_partner(V v) { return sw(v); }
 static inline float2 lane_partner2(float2 v) { return {sw(v.x), sw(v.y)}; }
 static inline void lane_partner4(float2 a, float2 b, float2& pa, float2& pb) { pa = lane_partner2(a); pb = lane_partner2(b); }
-template <class T> static inline const T& cg_kfence(const T& k) { return k; }
 template <int L> struct CgBody;
 template <int L> struct CgRealBody;
 template <int L> struct CgMirrorBody;
