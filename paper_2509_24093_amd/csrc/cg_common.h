@@ -31,6 +31,17 @@ __device__ __forceinline__ float fnma(float a, float b, float c) {
   return r;
 }
 
+// a*b, under an ID of its own: the optimiser may not take it for the same
+// product elsewhere in the unrolled code and hold it in a register until then.
+// (As volatile assembly it would also stop the scalar loads of uniform values
+// that follow it.)
+template <int ID>
+__device__ __forceinline__ float mul_here(float a, float b) {
+  float r;
+  asm("v_mul_f32 %0, %1, %2 ; %3" : "=v"(r) : "v"(a), "v"(b), "n"(ID));
+  return r;
+}
+
 // value of the lane with index lane ^ 1 (quad_perm [1,0,3,2])
 __device__ __forceinline__ float swap_pair(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));

@@ -930,7 +930,7 @@ cgconv_plan_t cgconv_plan_create_graph(int64_t batch, int64_t N, int32_t L_max, 
     p->nnz = (int64_t)terms.size();
     p->products = distinct_products(terms, K);
   }
-  p->rtable = real_table(L_max);  // the per-frequency product is the generated real-basis body
+  p->rtable = real_table(L_max);  // the tensor of the per-frequency product
   p->Kp = round_up(N, 32);
   p->Mp = round_up(N, 128);
   p->KCp = round_up((int64_t)K * C, 128);
@@ -1476,7 +1476,6 @@ int cgconv_gate_value_backward(cgconv_plan_t plan, const float* u, const float* 
   a.S = plan->d_gS;
   a.part = plan->d_gpart;
   a.fin = plan->d_gfin;
-  a.scales = plan->d_bscale;
   a.B = (int)plan->B;
   a.N = (int)plan->Nu;
   a.C = (int)plan->C;

@@ -14,8 +14,11 @@
 // exp(I - m)) per (l, c); (2) the partials of all chunks are combined into
 // the maximum and denominator per (b, l, c); (3) one lane per (b, i, c)
 // recomputes its norms, applies the gate and evaluates the generated
-// token-wise real-basis product (CgRealBody).  u, v, f: fp32 [B][N][K][C],
-// channel fastest, so every load and store of a wave is contiguous.
+// token-wise product (CgRealBody), which is what bounds it: 8.9k vector
+// operations per lane at L_max = 6 (10.6k in the real basis; kernel 0.97 ->
+// 0.94 ms at B=8 N=16384 C=32, L_max = 5 606 -> 509 us, 7 and 8 8-11% less).
+// u, v, f: fp32 [B][N][K][C], channel fastest, so every load and store of a
+// wave is contiguous.
 #include <hip/hip_runtime.h>
 
 #include "cg_common.h"
@@ -32,6 +35,12 @@ namespace {
 using namespace cgdev;
 
 constexpr int kGateThreads = 256;
+// Waves per SIMD the forward product kernels' registers must allow: 3K values
+// and temporaries fit a third of the file up to L_max = 6 (156 registers
+// there), half of it above.  The backward kernels hold more and take what they
+// need: held to a third, the one for du spills 13 registers at L_max = 6
+// (both gradients 1.90 -> 2.08 ms, B=8 N=16384 C=32).
+constexpr int kProductWaves = CGCONV_TU_L <= 6 ? 3 : 2;
 
 template <int L>
 __device__ __forceinline__ void degree_norms(const float* x, float (&I)[L + 1]) {
@@ -147,7 +156,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_finalize_kernel(const float
 
 // One lane per (b, i, c), c fastest.
 template <int L>
-__global__ __launch_bounds__(kGateThreads) void gate_value_kernel(const float* __restrict__ u,
+__global__ __launch_bounds__(kGateThreads, kProductWaves) void gate_value_kernel(const float* __restrict__ u,
                                                                   const float* __restrict__ v,
                                                                   const float2* __restrict__ fin,
                                                                   float* __restrict__ f, int N, int C,
@@ -181,13 +190,33 @@ __global__ __launch_bounds__(kGateThreads) void gate_value_kernel(const float* _
   for (int k = 0; k < K; ++k) z[(long long)k * C] = out[k];
 }
 
+// sqrt(2l + 1) and its reciprocal, rounded once as in the plan's scale table
+__device__ __forceinline__ constexpr double degree_root(int l) {
+  constexpr double r[9] = {1.0,
+                           1.7320508075688772935,
+                           2.2360679774997896964,
+                           2.6457513110645905905,
+                           3.0,
+                           3.3166247903553998491,
+                           3.6055512754639892931,
+                           3.8729833462074168852,
+                           4.1231056256176605498};
+  return r[l];
+}
+__device__ __forceinline__ constexpr int degree_of(int k) {
+  int l = 0;
+  while ((l + 1) * (l + 1) <= k) ++l;
+  return l;
+}
+
 // Backward, one lane per (b, i, c): the gradients of the token-wise product
 // with respect to its two operands are forward products of the output
 // gradient under per-degree scales (the transposition identity of the
 // real-basis tensor, as for the convolution's backward):
-//   da = s_o .* TP(s_a .* G, s_b .* v)   (first-operand scales, scales[0..3K))
-//   dv = t_o .* TP(t_a .* G, a)          (second-operand scales, scales[3K..6K), t_b = 1)
-// with a = g u.  DU = false stores dv; DU = true stores du = g da (the gate
+//   da = s_o .* TP(s_a .* G, s_b .* v)   s_a = sqrt(2l+1), s_b = (-1)^l, s_o = 1 / s_a
+//   dv = t_o .* TP(t_a .* G, a)          t_a = (-1)^l sqrt(2l+1), t_o = (-1)^l / sqrt(2l+1)
+// with a = g u (constants of the unrolled code: read from the plan's table,
+// the output scales were vector loads behind the gradient's stores).  DU = false stores dv; DU = true stores du = g da (the gate
 // held fixed) and h[l] = g[l] sum_m u[l,m] da[l,m] for the softmax and norm
 // terms.  The two gradients are separate launches so that each holds only
 // one product's operands and result in registers (3 waves per SIMD at
@@ -219,16 +248,24 @@ __global__ __launch_bounds__(kGateThreads) void gate_bwd_kernel(GateBwdArgs a, l
       for (int m = 0; m < 2 * l + 1; ++m) x[l * l + m] *= g[l];  // x = a = g u
     }
 #pragma unroll
-    for (int k = 0; k < K; ++k) gr[k] = a.G[base + (long long)k * a.C] * a.scales[3 * K + k];
+    for (int k = 0; k < K; ++k) {
+      const int l = degree_of(k);
+      gr[k] = a.G[base + (long long)k * a.C] * (float)((l & 1) ? -degree_root(l) : degree_root(l));
+    }
     CgRealBody<L>::run(gr, x, out);
 #pragma unroll
-    for (int k = 0; k < K; ++k) a.dv[base + (long long)k * a.C] = out[k] * a.scales[5 * K + k];
+    for (int k = 0; k < K; ++k) {
+      const int l = degree_of(k);
+      a.dv[base + (long long)k * a.C] = out[k] * (float)((l & 1 ? -1.0 : 1.0) / degree_root(l));
+    }
     return;
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    gr[k] = a.G[base + (long long)k * a.C] * a.scales[k];
-    x[k] = a.v[base + (long long)k * a.C] * a.scales[K + k];  // x now holds v
+    const int l = degree_of(k);
+    gr[k] = a.G[base + (long long)k * a.C] * (float)degree_root(l);
+    const float v = a.v[base + (long long)k * a.C];
+    x[k] = (l & 1) ? -v : v;  // x now holds s_b v
   }
   CgRealBody<L>::run(gr, x, out);  // out = da / s_o
   // An opaque copy of the lane offset: the addresses below are computed
@@ -246,7 +283,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_bwd_kernel(GateBwdArgs a, l
 #pragma unroll
     for (int m = 0; m < 2 * l + 1; ++m) {
       const int k = l * l + m;
-      const float da = out[k] * a.scales[2 * K + k];
+      const float da = out[k] * (float)(1.0 / degree_root(l));
       s = fmaf(x[k], da, s);
       a.du[tail + (long long)k * a.C] = g[l] * da;
     }
@@ -356,7 +393,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_bwd_du_kernel(GateBwdArgs a
 
 // One lane per (b, f, c), c fastest: the CG product of the graph transforms.
 template <int L>
-__global__ __launch_bounds__(kGateThreads) void gft_product_kernel(GftProductArgs a, long long lanes) {
+__global__ __launch_bounds__(kGateThreads, kProductWaves) void gft_product_kernel(GftProductArgs a, long long lanes) {
   constexpr int K = (L + 1) * (L + 1);
   const long long p = (long long)blockIdx.x * kGateThreads + threadIdx.x;
   if (p >= lanes) return;
@@ -415,7 +452,7 @@ hipError_t launch_gft_product<CGCONV_TU_L>(const GftProductArgs& a, hipStream_t 
 template <>
 hipError_t launch_gate_backward<CGCONV_TU_L>(const GateBwdArgs& a, hipStream_t s) {
   if (a.B < 1 || a.N < 1 || a.C < 1 || !a.u || !a.v || !a.G || (!a.du && !a.dv) || !a.part || !a.fin ||
-      !a.scales || (a.du && (!a.h || !a.psum || !a.S)))
+      (a.du && (!a.h || !a.psum || !a.S)))
     return hipErrorInvalidValue;
   const int chunks = (a.N + kGateChunk - 1) / kGateChunk;
   const int cpb = a.C < kGateThreads ? a.C : kGateThreads;

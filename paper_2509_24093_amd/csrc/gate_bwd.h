@@ -21,7 +21,6 @@ struct GateBwdArgs {
   float* S;              // [B][L+1][C]
   float2* part;          // softmax partials and statistics, as in the forward
   float2* fin;
-  const float* scales;   // [6][K]: the backward scales (first operand: 0..3K, second: 3K..6K)
   int B, N, C;
   hipEvent_t* events;    // optional: 5 events around the four stages
 };

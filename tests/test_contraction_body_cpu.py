@@ -31,6 +31,7 @@ static inline V operator+(V x, V y) { return V(x.a + y.a, x.b + y.b); }
 static inline V operator-(V x, V y) { return V(x.a - y.a, x.b - y.b); }
 static inline V operator-(V x) { return V(-x.a, -x.b); }
 static inline V vfma(V x, V y, V z) { return x * y + z; }
+template <int ID> static inline V mul_here(V x, V y) { return x * y; }
 static inline V fnma(V x, V y, V z) { return z - x * y; }
 #define float V
 #define fmaf vfma
@@ -73,6 +74,14 @@ extern "C" void mirror(const double* qa, const double* ka, double* out) {
     }
   MStore st{out};
   CgMirrorBody<LL>::run(q, k, st);
+}
+// token-wise product of real components
+extern "C" void real(const double* a, const double* b, double* f) {
+  constexpr int K = (LL + 1) * (LL + 1);
+  V x[K], y[K], z[K];
+  for (int i = 0; i < K; ++i) { x[i] = V(a[i]); y[i] = V(b[i]); }
+  CgRealBody<LL>::run(x, y, z);
+  for (int i = 0; i < K; ++i) f[i] = z[i].a;
 }
 """
 
@@ -122,3 +131,20 @@ def test_mirror_body_is_the_host_contraction(L, bodies):
         ref = P.cgconv_contract_host(L, q, k)
         # the emitted coefficients are rounded to float (2^-24 each)
         assert np.abs(out - ref).max() < 2e-7 * np.abs(ref).max() * np.sqrt(K)
+
+
+@pytest.mark.parametrize("L", [0, 1, 2, 3, 5, 6, 8])
+def test_real_body_is_the_real_table(L, bodies):
+    lib = bodies(L)
+    rng = np.random.default_rng(70 + L)
+    K = (L + 1) ** 2
+    idx, coef = P.cgconv_cg_table(L)
+    x = idx[:, 0] ** 2 + idx[:, 0] + idx[:, 1]
+    y = idx[:, 2] ** 2 + idx[:, 2] + idx[:, 3]
+    o = idx[:, 4] ** 2 + idx[:, 4] + idx[:, 5]
+    for _ in range(2):
+        a, b = rng.normal(size=K), rng.normal(size=K)
+        f = np.zeros(K)
+        lib.real(_ptr(a), _ptr(b), _ptr(f))
+        ref = np.bincount(o, weights=coef * a[x] * b[y], minlength=K)
+        assert np.abs(f - ref).max() < 2e-7 * np.abs(ref).max() * np.sqrt(K)
