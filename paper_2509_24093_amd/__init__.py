@@ -280,6 +280,16 @@ def cgconv_contract_host(L_max: int, qhat, khat):
 
 # ---- torch convenience -------------------------------------------------------
 
+def _current_stream(torch) -> int:
+    """Handle of torch's current stream on the current device.  The raw query
+    (where torch has it) skips the Stream object that
+    torch.cuda.current_stream() builds, 3 us of every call."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
+
+
 class Plan:
     """A plan for q, k, out of shape [batch, N, (L_max+1)^2, C] on the current
     GPU.  ``plan(q, k)`` returns out; fp32 or bfloat16 tensors.  ``boundary``
@@ -318,7 +328,7 @@ class Plan:
                 raise ValueError(f"{name} must be a GPU tensor")
             if tuple(t.shape) != self.shape or t.dtype != dtype or not t.is_contiguous():
                 raise ValueError(f"{name} must be a contiguous {dtype} tensor of shape {self.shape}")
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream(torch)
 
     def forward(self, q, k, out=None):
         import torch
@@ -372,7 +382,7 @@ class Plan:
         if (not out.is_cuda or tuple(out.shape) != (B, N, K, int(heads) * m_out) or out.dtype != torch.float32
                 or not out.is_contiguous()):
             raise ValueError(f"out must be a contiguous float32 GPU tensor of shape {(B, N, K, int(heads) * m_out)}")
-        s = torch.cuda.current_stream().cuda_stream
+        s = _current_stream(torch)
         cgconv_forward_interchannel(self._h, int(heads), m_out, q.data_ptr(), k.data_ptr(), weights.data_ptr(),
                                     out.data_ptr(), s)
         return out
@@ -395,10 +405,7 @@ class Plan:
             return None, None
         gu = torch.empty(self.shape, dtype=torch.float32, device=u.device) if need_u else None
         gv = torch.empty(self.shape, dtype=torch.float32, device=u.device) if need_v else None
-        s = self._args(u, v, grad_f, torch.float32)
-        for t in (gu, gv):
-            if t is not None:
-                self._args(t, t, t, torch.float32)
+        s = self._args(u, v, grad_f, torch.float32)  # (gu and gv are as allocated above)
         cgconv_gate_value_backward(self._h, u.data_ptr(), v.data_ptr(), grad_f.data_ptr(),
                                    gu.data_ptr() if gu is not None else None,
                                    gv.data_ptr() if gv is not None else None, s)
@@ -412,10 +419,7 @@ class Plan:
             return None, None
         gq = torch.empty(self.shape, dtype=torch.float32, device=q.device) if need_q else None
         gk = torch.empty(self.shape, dtype=torch.float32, device=q.device) if need_k else None
-        s = self._args(q, k, grad_out, torch.float32)
-        for name, t in (("grad_q", gq), ("grad_k", gk)):
-            if t is not None:
-                self._args(t, t, t, torch.float32)
+        s = self._args(q, k, grad_out, torch.float32)  # (gq and gk are as allocated above)
         cgconv_backward(self._h, q.data_ptr(), k.data_ptr(), grad_out.data_ptr(),
                         gq.data_ptr() if gq is not None else None, gk.data_ptr() if gk is not None else None, s)
         return gq, gk

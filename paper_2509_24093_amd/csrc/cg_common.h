@@ -12,7 +12,7 @@ namespace cgdev {
 template <int L>
 struct CgBody;  // specialised by the generated cg_body_L<L>.inc files
 template <int L>
-struct CgRealBody;  // token-wise real-basis product of the value tensor product (same files)
+struct CgRealBody;  // token-wise product of real components for the value tensor product (same files)
 template <int L>
 struct CgMirrorBody;  // lane-pair variant: one point per two lanes (same files)
 template <int L>

@@ -35,7 +35,7 @@
 // Further bodies per L: CgMirrorBody<L>, the lane-pair form of the same
 // contraction (emit_mirror_body); CgPathSplitBody<L>, which keeps the paths
 // apart for the channel-mixing kernel, in steps (emit_path_split_body); and
-// CgRealBody<L>, the token-wise real-basis product of the value tensor
+// CgRealBody<L>, the token-wise product of real components of the value tensor
 // product (emit_real_body).
 //
 // Usage: gen_cg <output-dir> <LGEN>   (writes cg_body_L<L>.inc and cg_lgen.h)
