@@ -66,7 +66,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak, published
 # sources of every kernel of the fused forward (the step's counter bytes
 # cover all three stages) and of the plan that launches them
 CG_SOURCES = ["paper_2509_24093_amd/csrc/cg_gen.hip", "paper_2509_24093_amd/csrc/cg_fused.hip",
-              "paper_2509_24093_amd/csrc/fft.hip", "paper_2509_24093_amd/csrc/cgconv.cpp",
+              "paper_2509_24093_amd/csrc/fft.hip", "paper_2509_24093_amd/csrc/fft_pass.h",
+              "paper_2509_24093_amd/csrc/cgconv.cpp",
               "paper_2509_24093_amd/csrc/cg_common.h", "paper_2509_24093_amd/csrc/fft_reg.h",
               "paper_2509_24093_amd/csrc/codegen/gen_cg.cpp", "paper_2509_24093_amd/csrc/cg_table.cpp",
               "paper_2509_24093_amd/csrc/kernels.h"]

@@ -167,6 +167,7 @@ constexpr int kKindGateBwd = 5;
 constexpr int kKindGraph = 4;
 constexpr int kKindInter = 6;
 constexpr int kKindSmall = 7;
+constexpr int kKindSmallBwd = 8;  // the one-launch backward
 constexpr int kMaxEvents = 8;  // stages + 1 of the longest pipeline
 
 hipError_t launch_product(int L, const GftProductArgs& a, hipStream_t s) {
@@ -1230,7 +1231,7 @@ int cgconv_plan_stage_times(cgconv_plan_t plan, double* ms, int32_t cap, int32_t
     return CGCONV_ERR_INVALID_ARG;
   }
   const int ns = plan->timing_kind == 1 || plan->timing_kind == kKindInter ? plan->n_stages_mix
-                 : plan->timing_kind == kKindSmall ? 1
+                 : plan->timing_kind == kKindSmall || plan->timing_kind == kKindSmallBwd ? 1
                  : plan->timing_kind == kKindGate  ? 3
                  : plan->timing_kind == kKindGateBwd ? 4
                  : plan->timing_kind == kKindGraph ? 6
@@ -1264,7 +1265,7 @@ const char* cgconv_plan_stage_name(cgconv_plan_t plan, int32_t stage) {
     if (stage >= plan->n_stages_mix) return "";
     return plan->N1 ? kStagesM2[stage] : kStagesM1[stage];
   }
-  if (plan->timing_kind == kKindSmall) return stage < 1 ? kStagesS[stage] : "";
+  if (plan->timing_kind == kKindSmall || plan->timing_kind == kKindSmallBwd) return stage < 1 ? kStagesS[stage] : "";
   if (plan->timing_kind == kKindGate) return stage < 3 ? kStagesG[stage] : "";
   if (plan->timing_kind == kKindGateBwd) return stage < 4 ? kStagesGB[stage] : "";
   if (plan->timing_kind == kKindGraph) return stage < 6 ? kStagesGft[stage] : "";
@@ -1385,8 +1386,8 @@ int cgconv_backward(cgconv_plan_t plan, const float* q, const float* k, const fl
     if (grad_q) pr[n++] = {grad_out, k, grad_q, plan->d_bscale};
     if (grad_k) pr[n++] = {grad_out, q, grad_k, plan->d_bscale + 3 * K};
     hipEvent_t* ev = nullptr;
-    if (plan->timing_calls < plan->timing_max && (plan->timing_kind < 0 || plan->timing_kind == kKindSmall)) {
-      plan->timing_kind = kKindSmall;
+    if (plan->timing_calls < plan->timing_max && (plan->timing_kind < 0 || plan->timing_kind == kKindSmallBwd)) {
+      plan->timing_kind = kKindSmallBwd;
       ev = &plan->events[(size_t)plan->timing_calls * kMaxEvents];
       ++plan->timing_calls;
     }
