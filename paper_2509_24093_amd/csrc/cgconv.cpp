@@ -812,8 +812,10 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
     delete p;
     return nullptr;
   }
+  // the allowance belongs to the kernel, which other plans use too: always the
+  // largest, never this plan's own size
   if ((p->small_fwd || p->small_bwd) && small_lds_bytes(N, K, p->small_cc) > 64 * 1024 &&
-      (e = prepare_small(L_max, (int)small_lds_bytes(N, K, p->small_cc))) != hipSuccess) {
+      (e = prepare_small(L_max, kSmallMaxLds)) != hipSuccess) {
     set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e));
     delete p;
     return nullptr;
