@@ -30,8 +30,9 @@
 // Bound by latency: one lane's chain of loads, LDS exchanges and dependent
 // operations (of 47k cycles at B=32, N=32, L_max=4, C=32 with one lane group
 // per point, 20k were the contraction's 2.6k operations, which two groups
-// halve).  Measured at that shape: forward 23.7 -> 19.4 us, both gradients
-// 52.5 us in six launches of the three kernels -> 23.3 us.
+// halve).  Measured at that shape: forward 17.8 us (23.4 with the lane pair
+// that held q in one lane and k in the other), both gradients 22.1 us (52.4 in
+// the six launches of the three kernels).
 #include <hip/hip_runtime.h>
 
 #include "cg_common.h"
@@ -68,7 +69,8 @@ __device__ __forceinline__ int divm(int x, uint32_t m) { return m ? (int)__umulh
 // at row R2 f1 + f2.  tw[j] = exp(-2 pi i j / Nf), j < Nf; DIR = +1: inverse
 // (conjugate twiddles).  mc = the division magic of cols.
 template <int R1, int R2, int DIR>
-__device__ void dft_columns(float2* Z, const float2* tw, int cols, uint32_t mc, int tid, int nthreads) {
+__device__ __forceinline__ void dft_columns(float2* Z, const float2* tw, int cols, uint32_t mc, int tid,
+                                            int nthreads) {
   __syncthreads();
   // stage 1: per (column, n2), rows R2 n1 + n2 -> radix R1 -> x W^(n2 f1)
   for (int it = tid; it < R2 * cols; it += nthreads) {
@@ -103,7 +105,8 @@ __device__ void dft_columns(float2* Z, const float2* tw, int cols, uint32_t mc, 
 }
 
 template <int DIR>
-__device__ void dft_any(int lg, float2* Z, const float2* tw, int cols, uint32_t mc, int tid, int nthreads) {
+__device__ __forceinline__ void dft_any(int lg, float2* Z, const float2* tw, int cols, uint32_t mc, int tid,
+                                        int nthreads) {
   switch (lg) {  // uniform: Nf = R1 * R2
     case 1: dft_columns<2, 1, DIR>(Z, tw, cols, mc, tid, nthreads); break;
     case 2: dft_columns<4, 1, DIR>(Z, tw, cols, mc, tid, nthreads); break;
@@ -137,54 +140,71 @@ struct SmallStore {
   __device__ __forceinline__ void end_phase(int) const {}
 };
 
-template <int L>
-__global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArgs a) {
+// Waves per SIMD the registers must allow: up to L_max 3 the radix-16 DFTs hold
+// the most, 70 VGPRs, seven waves, when held to it; left alone the forward takes
+// 85, and blocks of five or nine waves no longer share a CU (B=512 N=64 L=0 C=8:
+// 6.5 us held, 9.4 not).  Above, the contraction's registers decide (at L_max 4
+// six waves would spill).
+constexpr int small_waves(int L) { return L <= 3 ? 6 : 1; }
+
+// ADJ: the adjoint form, one or two problems; otherwise the forward of problem
+// 0, without the reversed rows, the scales and the choice of a problem (L=0,
+// B=1 N=8 C=3, where the launch is all there is: 4.9 us for one kernel of both
+// forms, 4.1 us).
+template <int L, bool ADJ>
+__global__ __launch_bounds__(small_max_threads(L), small_waves(L)) void cg_small_kernel(SmallArgs a) {
   constexpr int K = (L + 1) * (L + 1);
   extern __shared__ __attribute__((aligned(16))) float2 smem[];
   const int Nf = a.Nf, lg = a.lg, cc = a.cc, cq = cc >> 1;
   const int tid = threadIdx.x, nthreads = blockDim.x;
   const int b = blockIdx.x / a.groups, grp = blockIdx.x % a.groups;
   const int c0 = grp * cc;  // first channel of the group
-  const SmallProblem pr = a.problem[blockIdx.y];
+  const SmallProblem pr = a.problem[ADJ ? blockIdx.y : 0];
   float2* Z = smem;                 // [Nf][K][cc]
   float2* tw = smem + Nf * K * cc;  // [Nf]
   const int colsZ = K * cc, colsV = K * cq;
 
   for (int j = tid; j < Nf; j += nthreads) tw[j] = a.tw[j];
   // 1. load q + i k: kInFlight elements per thread at a time.  The adjoint
-  // form (pr.scales) scales both operands per component and reads the rows
-  // of the second one reversed.
+  // form scales both operands per component and reads the rows of the second
+  // one reversed.
   constexpr int kInFlight = 8;
   const long long in_b = (long long)b * a.in_rows * K * a.C;
   const int totalZ = Nf * colsZ;
-  const bool adj = pr.scales != nullptr;
   for (int base = 0; base < totalZ; base += kInFlight * nthreads) {
-    float2 z[kInFlight], sc[kInFlight];
+    float2 z[kInFlight];
+    [[maybe_unused]] float2 sc[kInFlight];
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) {
       const int it = base + u * nthreads + tid;
       const int n = divm(it, a.mz), col = it - n * colsZ;
       const int k = col >> a.lcc, c = col & (cc - 1);
       const int ch = c0 + c < a.C ? c0 + c : a.C - 1;
-      const int n1 = adj ? (-n) & (Nf - 1) : n;
+      const int n1 = ADJ ? (-n) & (Nf - 1) : n;
       z[u] = make_float2(0.f, 0.f);
       const bool in0 = it < totalZ && n < a.in_rows, in1 = it < totalZ && n1 < a.in_rows;
-      const uint32_t off0 = ((uint32_t)n * K + k) * (uint32_t)a.C + ch, off1 = ((uint32_t)n1 * K + k) * (uint32_t)a.C + ch;
-      if (a.bf16) {
-        const uint16_t* q16 = static_cast<const uint16_t*>(pr.q) + in_b;
-        const uint16_t* k16 = static_cast<const uint16_t*>(pr.k) + in_b;
-        if (in0) z[u].x = __uint_as_float((uint32_t)q16[off0] << 16);
-        if (in1) z[u].y = __uint_as_float((uint32_t)k16[off1] << 16);
-      } else {
-        if (in0) z[u].x = (static_cast<const float*>(pr.q) + in_b)[off0];
-        if (in1) z[u].y = (static_cast<const float*>(pr.k) + in_b)[off1];
+      const uint32_t off0 = ((uint32_t)n * K + k) * (uint32_t)a.C + ch;
+      const uint32_t off1 = ((uint32_t)n1 * K + k) * (uint32_t)a.C + ch;
+      const float* q32 = static_cast<const float*>(pr.q) + in_b;
+      const float* k32 = static_cast<const float*>(pr.k) + in_b;
+      if constexpr (ADJ) {
+        if (in0) z[u].x = q32[off0];
+        if (in1) z[u].y = k32[off1];
+        if (it < totalZ) sc[u] = make_float2(pr.scales[k], pr.scales[K + k]);
+      } else if (in0) {
+        if (a.bf16) {
+          const uint16_t* q16 = static_cast<const uint16_t*>(pr.q) + in_b;
+          const uint16_t* k16 = static_cast<const uint16_t*>(pr.k) + in_b;
+          z[u] = make_float2(__uint_as_float((uint32_t)q16[off0] << 16), __uint_as_float((uint32_t)k16[off0] << 16));
+        } else {
+          z[u] = make_float2(q32[off0], k32[off0]);
+        }
       }
-      if (adj && it < totalZ) sc[u] = make_float2(pr.scales[k], pr.scales[K + k]);
     }
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) {
       const int it = base + u * nthreads + tid;
-      if (it < totalZ) Z[it] = adj ? make_float2(z[u].x * sc[u].x, z[u].y * sc[u].y) : z[u];
+      if (it < totalZ) Z[it] = ADJ ? make_float2(z[u].x * sc[u].x, z[u].y * sc[u].y) : z[u];
     }
   }
   // 2. forward DFT of every column
@@ -199,8 +219,11 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
   // the block waits for here.
   {
     const int npts = ((Nf >> 1) + 1) * cc;
-    const int lanes = nthreads / a.parts;  // whole waves
-    const int part = __builtin_amdgcn_readfirstlane(tid / lanes);
+    // (compared, not divided: two integer divisions ahead of the gather cost
+    // 0.5 us of a launch)
+    const int lanes = a.lanes;  // whole waves
+    const int part = __builtin_amdgcn_readfirstlane((tid >= lanes) + (tid >= 2 * lanes) + (tid >= 3 * lanes));
+    const uint32_t phases = part < 2 ? (part == 0 ? a.phases[0] : a.phases[1]) : (part == 2 ? a.phases[2] : a.phases[3]);
     const int lt = tid - part * lanes;
     const int half = lt & 1;
     const int p = lt >> 1;
@@ -239,7 +262,7 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
     // row w again with the conjugate: it writes the trash row instead
     const bool write = valid && (st.even || wn != w);
     st.row = write ? (st.even ? w : wn) : Nf;
-    CgMirrorBody<L>::run(q, k, st, a.phases[part]);
+    CgMirrorBody<L>::run(q, k, st, phases);
   }
   // 5. inverse DFT of every packed column, scale and store (time n at row
   // R2 (n mod R1) + n / R1)
@@ -248,14 +271,14 @@ __global__ __launch_bounds__(small_max_threads(L)) void cg_small_kernel(SmallArg
   const long long out_b = (long long)b * a.out_rows * K * a.C;
   const int totalV = a.out_rows * colsV;
   const bool even_c = (a.C & 1) == 0;
-#pragma unroll 4
+#pragma unroll 1  // four at a time: 0.1 us more per launch, nothing gained at any length
   for (int it = tid; it < totalV; it += nthreads) {
     const int n = divm(it, a.mv), col = it - n * colsV;
     const int k = col >> (a.lcc - 1), pi = col & (cq - 1);
     float2 v = Z[row_of(n) * colsV + col];
     v.x *= inv;
     v.y *= inv;
-    if (adj) {
+    if constexpr (ADJ) {
       const float so = pr.scales[2 * K + k];
       v.x *= so;
       v.y *= so;
@@ -286,10 +309,12 @@ hipError_t launch_cg_small<CGCONV_TU_L>(const SmallArgs& a, hipStream_t s) {
   const int cc = 1 << a.lcc;
   if (a.Nf < 2 || a.Nf > kSmallMaxNf || (1 << a.lg) != a.Nf || a.lcc < 1 || a.lcc > 4 || a.cc != cc ||
       a.threads < 64 || a.threads > small_max_threads(CGCONV_TU_L) || (a.threads & 63) ||
-      a.parts < 1 || a.parts > kSmallMaxParts || a.threads % (64 * a.parts) != 0 || 2 * ((a.Nf / 2 + 1) * cc) * a.parts > a.threads ||
-      a.problems < 1 || a.problems > 2 || a.groups != (a.C + cc - 1) / cc || a.in_rows > a.Nf ||
+      a.parts < 1 || a.parts > kSmallMaxParts || a.lanes * a.parts != a.threads || (a.lanes & 63) ||
+      2 * ((a.Nf / 2 + 1) * cc) > a.lanes || a.problems < 1 || a.problems > 2 || a.groups != (a.C + cc - 1) / cc || a.in_rows > a.Nf ||
       a.out_rows > a.Nf || a.mz != 0xFFFFFFFFu / (uint32_t)(K * cc) + 1 || a.mv != 0xFFFFFFFFu / (uint32_t)(K * cc / 2) + 1)
     return hipErrorInvalidValue;
+  const bool adjoint = a.problem[0].scales != nullptr;  // (fp32 only; a forward is one problem)
+  if (adjoint ? a.bf16 || (a.problems == 2 && !a.problem[1].scales) : a.problems != 1) return hipErrorInvalidValue;
   const size_t lds = ((size_t)a.Nf * K * cc + a.Nf) * sizeof(float2);
   if (lds > kSmallMaxLds) return hipErrorInvalidValue;
   // the phases of each part: the longest first, each to the part with the
@@ -309,8 +334,11 @@ hipError_t launch_cg_small<CGCONV_TU_L>(const SmallArgs& a, hipStream_t s) {
     args.phases[part] |= 1u << mu;
     left &= ~(1u << mu);
   }
-  hipLaunchKernelGGL(cg_small_kernel<CGCONV_TU_L>, dim3((unsigned)(a.B * a.groups), a.problems), dim3(a.threads), lds,
-                     s, args);
+  const dim3 grid((unsigned)(a.B * a.groups), a.problems);
+  if (adjoint)
+    hipLaunchKernelGGL((cg_small_kernel<CGCONV_TU_L, true>), grid, dim3(a.threads), lds, s, args);
+  else
+    hipLaunchKernelGGL((cg_small_kernel<CGCONV_TU_L, false>), grid, dim3(a.threads), lds, s, args);
   return hipGetLastError();
 }
 
@@ -318,8 +346,12 @@ hipError_t launch_cg_small<CGCONV_TU_L>(const SmallArgs& a, hipStream_t s) {
 // device before the launch; the plan does it when it is created.
 template <>
 hipError_t prepare_cg_small<CGCONV_TU_L>(int lds_bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&cg_small_kernel<CGCONV_TU_L>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  for (const void* f : {reinterpret_cast<const void*>(&cg_small_kernel<CGCONV_TU_L, false>),
+                        reinterpret_cast<const void*>(&cg_small_kernel<CGCONV_TU_L, true>)}) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace cgconv

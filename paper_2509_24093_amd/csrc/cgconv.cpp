@@ -335,7 +335,8 @@ hipError_t run_small(const cgconv_plan* p, const SmallProblem* pr, int n, bool b
     while (2 * sa.parts <= std::min(p->L <= 2 ? 2 : kSmallMaxParts, p->L + 1) &&
            2 * sa.parts * p->small_lanes <= small_max_threads(p->L))
       sa.parts *= 2;
-  sa.threads = sa.parts * p->small_lanes;
+  sa.lanes = p->small_lanes;
+  sa.threads = sa.parts * sa.lanes;
   sa.bf16 = bf16;
   return launch_small(p->L, sa, s);
 }

@@ -194,9 +194,10 @@ hipError_t launch_cg_fused(const FusedArgs& a, hipStream_t s);
 // in_rows are zero (zero-padded plans).  scales != nullptr: the adjoint form
 // out = s_o conv(s_a q, s_b reverse(k)) with per-component scales [s_a, s_b,
 // s_o][K].  cc = 2^lcc channels per block (2 .. 16), groups = ceil(C / cc)
-// blocks per batch element, problems (1 or 2) independent convolutions of one
-// launch; parts (1 .. 4) lane groups share a point's outputs, each of whole
-// waves and at least 2 * (Nf/2 + 1) * cc threads (one lane pair per point).
+// blocks per batch element, problems (1 or, in the adjoint form, 2) independent
+// convolutions of one launch; parts (1 .. 4) lane groups share a point's
+// outputs, each of `lanes` threads: whole waves and at least 2 * (Nf/2 + 1) * cc
+// (one lane pair per point).
 // mz, mv: floor((2^32 - 1) / d) + 1 for d = K * cc and K * cc / 2 (divisions
 // by multiply-high).
 constexpr int kSmallMaxParts = 4;
@@ -209,7 +210,7 @@ struct SmallProblem {
 struct SmallArgs {
   SmallProblem problem[2];
   const float2* tw;  // exp(-2 pi i j / Nf), j < Nf
-  int B, C, Nf, lg, in_rows, out_rows, cc, lcc, groups, threads, parts, problems;
+  int B, C, Nf, lg, in_rows, out_rows, cc, lcc, groups, threads, lanes, parts, problems;
   uint32_t mz, mv;
   uint32_t phases[kSmallMaxParts];  // bit mu: the part evaluates the outputs |M| = mu (set by the launcher)
   bool bf16;

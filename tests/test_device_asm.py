@@ -121,3 +121,20 @@ def test_no_dpp_read_within_two_wait_states_of_its_write(unit, gen_dir, tmp_path
     assert n_dpp > 0, "no DPP instruction found: the scan would check nothing"
     bad = dpp_hazards(text)
     assert not bad, "%d DPP reads too close to their VALU write, e.g. %r" % (len(bad), bad[:3])
+
+
+@pytest.mark.parametrize("L", [0, 3])
+def test_one_block_kernel_leaves_room_for_seven_waves(L, gen_dir, tmp_path):
+    # 512 registers per SIMD lane: with more than 72 per wave, blocks of five
+    # and nine waves no longer share a CU as the launch rule assumes
+    out = str(tmp_path / "k.s")
+    cmd = [HIPCC, "-S", "--offload-device-only", "--offload-arch=gfx950", "-O3", "-std=c++17",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-I" + str(gen_dir), "-I" + CSRC, "-I" + INCLUDE,
+           "-DCGCONV_TU_L=%d" % L, '-DCGCONV_BODY="cg_body_L%d.inc"' % L, os.path.join(CSRC, "cg_small.hip"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    text = open(out).read()
+    vgprs = [int(v) for v in re.findall(r"^; TotalNumVgprs: (\d+)", text, re.M)]
+    scratch = [int(v) for v in re.findall(r"^; ScratchSize: (\d+)", text, re.M)]
+    assert vgprs and max(vgprs) <= 72 and max(scratch) == 0, (vgprs, scratch)
