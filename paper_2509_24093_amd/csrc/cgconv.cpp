@@ -76,6 +76,99 @@ int64_t linear_dft_length(int64_t N) {
   return best;
 }
 
+// LDS bytes of the one-block kernel for cc channels per block
+int64_t small_lds_bytes(int64_t Nf, int K, int cc) { return (Nf * K * cc + Nf) * 8; }
+
+struct SmallShape {
+  bool use = false;  // the one-block kernel rather than the three kernels per convolution
+  int cc = 0, lanes = 0, parts = 0;
+};
+
+// Launch shape of the one-block kernel for n = 1 or 2 convolutions of DFT
+// length Nf <= 256 over `rows` tokens (rows < Nf: zero-padded), and whether it
+// is used.  The figures are us in a replayed graph, from 3750 shapes (B 1..512,
+// Nf 4..256, L_max 0..6, C 1..64, cyclic and zero-padded) timed with every
+// channel group, every number of parts and the three kernels; the choice is
+// within 2-4% of the best of them on average.
+SmallShape small_shape(int64_t B, int64_t rows, int64_t Nf, int L, int64_t C, int n) {
+  SmallShape r;
+  const int K = (L + 1) * (L + 1);
+  const int max_threads = small_max_threads(L);
+  auto lanes = [&](int c) { return (int)((2 * (Nf / 2 + 1) * c + 63) / 64 * 64); };
+  auto fits = [&](int c) { return lanes(c) <= max_threads && small_lds_bytes(Nf, K, c) <= kSmallMaxLds; };
+  auto groups = [&](int c) { return (C + c - 1) / c; };
+  auto blocks = [&](int c) { return n * B * groups(c); };
+  // Channels per block (a power of two, 2 .. 16): the fewest that leave at most
+  // 128 blocks per convolution, or else the most that fit the thread and LDS
+  // limits, since small blocks reread every cache line of a row once per group
+  // (B=128 N=16 L=2 C=64, 2 / 4 / 8 / 16 channels: 21.3, 19.2, 14.1, 9.7).
+  const int64_t line = std::min<int64_t>(C, 32);  // channels of a 128-byte line that are this row's
+  int top = 16;
+  while (top > 2 && (top / 2 >= C || !fits(top))) top /= 2;
+  int cc = 2;
+  while (2 * cc <= 16 && cc < C && blocks(cc) > 128 * n && fits(2 * cc)) {
+    // not where the wider group's lanes would be padding (B=512 N=32 L=0 C=24: 8
+    // channels 10.1, 16 13.7; at L_max 5, 6 any padding of the channels: B=400
+    // N=32 L=5 C=10, 4 channels 67.9, 8 100.9), unless the blocks can then have
+    // a CU each (B=128 N=8 L=6 C=24: 8 channels 45.9, 16 24.1)
+    const bool wasted = 100 * groups(2 * cc) * lanes(2 * cc) > 115 * groups(cc) * lanes(cc) ||
+                        (L >= 5 && Nf >= 16 && 100 * 2 * groups(2 * cc) > 115 * groups(cc));
+    if (wasted && (blocks(cc) <= kSmallFewBlocks || blocks(top) > kSmallFewBlocks)) break;
+    // L_max 0 has no contraction to speak of: several small blocks per CU cover
+    // each other's loads (B=512 N=64 C=16: 4 channels 13.1, 8 15.1)
+    if (L == 0 && blocks(2 * cc) > kSmallFewBlocks && lanes(2 * cc) > 320) break;
+    // not if the point could then no longer be shared by two parts (B=128 N=128
+    // L=3 C=4: 2 channels 16.6, 4 18.4), unless little of a line is used (B=16
+    // N=64 L=2 C=64: 4 channels 13.5, 8 10.5); two gradients gain more from the
+    // wider group (B=32 N=128 L=3 C=16: 37.3, 27.8)
+    if (n == 1 && L >= 2 && line <= 4 * cc && blocks(cc) <= kSmallFewBlocks && 2 * lanes(cc) <= max_threads &&
+        2 * lanes(2 * cc) > max_threads)
+      break;
+    cc *= 2;
+  }
+  if (!fits(cc)) return r;
+  r.cc = cc;
+  r.lanes = lanes(cc);
+  // While every block has a CU of its own, the contraction waits for one lane's
+  // chain of operations, which two or four parts shorten (L=6 B=1 N=16 C=8: 36
+  // with one part, 21 with two, 16 with four).  With more blocks the lanes
+  // compete (L=2 B=512 N=16 C=8: 8.9, 9.7, 10.8).
+  r.parts = 1;
+  if (blocks(cc) <= kSmallFewBlocks)
+    while (2 * r.parts <= std::min(L <= 2 ? 2 : kSmallMaxParts, L + 1) && 2 * r.parts * r.lanes <= max_threads)
+      r.parts *= 2;
+  // Against the three kernels.  Their passes read whole rows; a block reads cc
+  // of every C channels, so each 128-byte line (32 channels) is read line / cc
+  // times, more where the last group is padded, less where rows are zeros.
+  // The one-block kernel wins up to a number of spectrum elements per CU that
+  // falls with that factor (columns: up to 2, up to 4, above) and grows with
+  // the contraction, which both do alike (one block / three kernels): L=0 N=128
+  // C=16 B=128 7.9 / 13.5, B=512 30.0 / 20.1; L=1 N=64 C=64 B=32 7.7 / 14.9, B=128
+  // 24.6 / 22.7; L=2 N=256 C=32 B=8 21.0 / 21.1, B=32 38.1 / 27.2; L=4 N=32 C=32
+  // B=64 23.2 / 28.9, B=128 38.5 / 36.4; L=6 N=64 C=16 B=32 46.3 / 61.9, B=64 79.9 /
+  // 67.2.  From L_max 3 rows of more than 64 channels stay with the three kernels
+  // once the blocks outnumber the CUs (B=64 N=16 L=5 C=100, both gradients 119 /
+  // 96; below, L=2 B=16 N=64 C=100 14.6 / 19.9).
+  static constexpr int kMost[7][3] = {{2600, 2200, 1200},  {10000, 7000, 4200},  {26000, 10000, 3500},
+                                      {26000, 7500, 4500}, {26000, 11000, 6400}, {24000, 11000, 6400},
+                                      {24000, 11000, 6400}};
+  if (L >= 3 && C > 64 && B * groups(cc) > kSmallFewBlocks) return r;
+  double reread = (double)line / cc;
+  if (rows < Nf) reread = 1 + (reread - 1) * (double)rows / (double)Nf;
+  reread *= (double)(groups(cc) * cc) / (double)C;
+  double most = kMost[L][reread <= 2 ? 0 : (reread <= 4 ? 1 : 2)];
+  if (n == 2) {
+    most *= 1.45;  // six launches in place of three (L=2 N=256 C=64 B=8: 40.4 / 53.6, one gradient 26.9 / 25.5)
+  } else if (Nf >= 128 && L >= 3) {
+    // long columns of many components are serial work of few lanes: never where
+    // little of a line is used (B=1 N=256 L=3 C=16 25.0 / 20.5), less at 256 rows
+    if (reread > (Nf == 256 ? 4 : 6)) return r;
+    if (Nf == 256) most *= 0.75;
+  }
+  r.use = (double)(B * C * K) * 0.5 * (double)(rows + Nf) < 256.0 * most;
+  return r;
+}
+
 }  // namespace
 
 struct cgconv_plan {
@@ -94,10 +187,9 @@ struct cgconv_plan {
   int L = 0, K = 0;
   int64_t N1 = 0, N2 = 0;  // N1 == 0: single pass
   bool fused = false;      // two-pass with N2 = 64 and the fused middle kernel
-  // DFT length <= 256: the forward / the backward is one block per channel
-  // group (cg_small.hip) of small_cc channels, small_lanes threads per part
-  bool small_fwd = false, small_bwd = false;
-  int small_cc = 0, small_lanes = 0;
+  // DFT length <= 256: launches of the one-block kernel (cg_small.hip) for one
+  // and for two convolutions (a forward or one gradient; both gradients)
+  SmallShape small[2];
   int device = 0;
   int64_t nnz = 0, paths = 0, products = 0;  // nnz: complex-basis terms the contraction evaluates
   // the real-basis tensor the plan's kernels evaluate (cgconv_plan_export_table)
@@ -267,9 +359,6 @@ hipError_t prepare_small(int L, int lds_bytes) {
   }
 }
 
-// LDS bytes of the one-block kernel for cc channels per block
-int64_t small_lds_bytes(int64_t Nf, int K, int cc) { return (Nf * K * cc + Nf) * 8; }
-
 hipError_t launch_fused(int L, const FusedArgs& a, hipStream_t s) {
   switch (L) {
     case 0: return launch_cg_fused<0>(a, s);
@@ -319,23 +408,14 @@ hipError_t run_small(const cgconv_plan* p, const SmallProblem* pr, int n, bool b
   sa.lg = ilog2(p->N);
   sa.in_rows = (int)p->Nu;
   sa.out_rows = (int)p->Nu;
-  sa.cc = p->small_cc;
-  sa.lcc = ilog2(p->small_cc);
-  sa.mz = 0xFFFFFFFFu / (uint32_t)(p->K * p->small_cc) + 1;
-  sa.mv = 0xFFFFFFFFu / (uint32_t)(p->K * p->small_cc / 2) + 1;
-  sa.groups = (int)((p->C + p->small_cc - 1) / p->small_cc);
-  // While every block has a CU of its own, the contraction waits for one
-  // lane's chain of operations: more lanes per point (parts) shorten it (L=6
-  // B=1 N=16 C=8 forward: 36 us with one part, 21 with two, 16 with four; L=4
-  // B=32 N=32 C=32: 24, 19).  With more blocks the lanes compete and one part
-  // is the fastest (L=2 B=512 N=16 C=8: 8.9, 9.7, 10.8).
-  const long long blocks = (long long)p->B * sa.groups * n;
-  sa.parts = 1;
-  if (blocks <= kSmallFewBlocks)
-    while (2 * sa.parts <= std::min(p->L <= 2 ? 2 : kSmallMaxParts, p->L + 1) &&
-           2 * sa.parts * p->small_lanes <= small_max_threads(p->L))
-      sa.parts *= 2;
-  sa.lanes = p->small_lanes;
+  const SmallShape& shape = p->small[n - 1];
+  sa.cc = shape.cc;
+  sa.lcc = ilog2(shape.cc);
+  sa.mz = 0xFFFFFFFFu / (uint32_t)(p->K * shape.cc) + 1;
+  sa.mv = 0xFFFFFFFFu / (uint32_t)(p->K * shape.cc / 2) + 1;
+  sa.groups = (int)((p->C + shape.cc - 1) / shape.cc);
+  sa.lanes = shape.lanes;
+  sa.parts = shape.parts;
   sa.threads = sa.parts * sa.lanes;
   sa.bf16 = bf16;
   return launch_small(p->L, sa, s);
@@ -401,7 +481,7 @@ int run_forward(cgconv_plan* p, const void* q, const void* k, void* out, bool bf
   const long long Nu = p->Nu;  // rows of q, k and out (padded rows are implicit zeros)
   const float inv_n = 1.0f / (float)N;
   hipEvent_t* ev = nullptr;  // events of this call if it is timed
-  const bool small = p->small_fwd && !mix && !scales;
+  const bool small = p->small[0].use && !mix && !scales;
   const int kind = mix ? 1 : (scales ? 2 : (small ? kKindSmall : 0));  // 2: one half of a backward
   if (p->timing_calls < p->timing_max && (p->timing_kind < 0 || p->timing_kind == kind)) {
     p->timing_kind = kind;
@@ -777,36 +857,9 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
   }
   p->n_stages = (p->N1 && !p->fused) ? 5 : 3;
   p->n_stages_mix = p->N1 ? 5 : 3;
-  // DFT length <= 256: the one-block kernel.  Channels per block: the fewest
-  // (a power of two, 2 .. 16) that leave at most 128 blocks, i.e. one block
-  // per CU also for the two gradients of a backward, or else the most that
-  // fit the thread and LDS limits (small blocks reread every cache line of a
-  // row once per channel group).
   const char* no_small = std::getenv("CGCONV_NO_SMALL");
-  if (N <= kSmallMaxNf && L_max <= kSmallLmax && !p->force_generic && !(no_small && no_small[0] == '1')) {
-    auto lanes = [&](int c) { return (2 * (N / 2 + 1) * c + 63) / 64 * 64; };
-    auto fits = [&](int c) {
-      return lanes(c) <= small_max_threads(L_max) && small_lds_bytes(N, K, c) <= kSmallMaxLds;
-    };
-    int cc = 2;
-    while (2 * cc <= 16 && cc < 2 * Cp && batch * ((C + cc - 1) / cc) > 128 && fits(2 * cc)) cc *= 2;
-    if (fits(cc)) {
-      // Against the three kernels, whose loads read whole rows (us, forward
-      // one block / three kernels, then backward): at most one block per CU
-      // the one-block kernel wins (B=32 N=32 L=4 C=32 19 / 25, 23 / 53) but
-      // for long forward rows of which a block reads less than a quarter
-      // (B=16 N=256 L=3 C=16 32 / 26, 41 / 54; B=4 N=128 L=4 C=16 24 / 22,
-      // 27 / 48); with more blocks it wins where a block reads half a row, in
-      // the backward a quarter (B=256 N=32 L=3 C=32 at 16 channels 30 / 34,
-      // 66 / 68; B=128 N=64 L=4 C=16 at 4 41 / 38, 71 / 78; B=64 N=32 L=4
-      // C=64 at 8 40 / 36, B=64 N=64 L=3 C=64 at 8 39 / 34, 82 / 68).
-      const bool few = batch * ((C + cc - 1) / cc) <= kSmallFewBlocks;
-      p->small_fwd = few ? (N <= 64 || 4 * cc >= C) : 2 * cc >= C;
-      p->small_bwd = few || 4 * cc >= C;
-      p->small_cc = cc;
-      p->small_lanes = (int)lanes(cc);
-    }
-  }
+  if (N <= kSmallMaxNf && L_max <= kSmallLmax && !p->force_generic && !(no_small && no_small[0] == '1'))
+    for (int n = 1; n <= 2; ++n) p->small[n - 1] = small_shape(batch, N_tokens, N, L_max, C, n);
   hipError_t e = hipGetDevice(&p->device);
   if (e != hipSuccess) {
     set_error("hipGetDevice failed: %s", hipGetErrorString(e));
@@ -815,7 +868,8 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
   }
   // the allowance belongs to the kernel, which other plans use too: always the
   // largest, never this plan's own size
-  if ((p->small_fwd || p->small_bwd) && small_lds_bytes(N, K, p->small_cc) > 64 * 1024 &&
+  if (std::any_of(p->small, p->small + 2,
+                  [&](const SmallShape& r) { return r.use && small_lds_bytes(N, K, r.cc) > 64 * 1024; }) &&
       (e = prepare_small(L_max, kSmallMaxLds)) != hipSuccess) {
     set_error("hipFuncSetAttribute failed: %s", hipGetErrorString(e));
     delete p;
@@ -1382,8 +1436,8 @@ int cgconv_backward(cgconv_plan_t plan, const float* q, const float* k, const fl
     return CGCONV_ERR_INVALID_ARG;
   }
   const int K = plan->K;
-  if (plan->small_bwd) {
-    // both gradients in one launch of the one-block kernel
+  if (plan->small[grad_q && grad_k ? 1 : 0].use) {
+    // one launch of the one-block kernel, also for both gradients
     SmallProblem pr[2];
     int n = 0;
     if (grad_q) pr[n++] = {grad_out, k, grad_q, plan->d_bscale};
