@@ -168,7 +168,10 @@ __global__ __launch_bounds__(small_max_threads(L), small_waves(L)) void cg_small
   // 1. load q + i k: kInFlight elements per thread at a time.  The adjoint
   // form scales both operands per component and reads the rows of the second
   // one reversed.
-  constexpr int kInFlight = 8;
+  // (eight: the same with many elements per thread, but with few the code that
+  // finds nothing to load is what a block runs, 4-7% of a launch at L_max 0, 1; two
+  // wait more often, up to 5% above L_max 2)
+  constexpr int kInFlight = 4;
   const long long in_b = (long long)b * a.in_rows * K * a.C;
   const int totalZ = Nf * colsZ;
   for (int base = 0; base < totalZ; base += kInFlight * nthreads) {
