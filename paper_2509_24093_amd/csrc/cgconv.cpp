@@ -141,7 +141,7 @@ SmallShape small_shape(int64_t B, int64_t rows, int64_t Nf, int L, int64_t C, in
   // of every C channels, so each 128-byte line (32 channels) is read line / cc
   // times, more where the last group is padded, less where rows are zeros.
   // The one-block kernel wins up to a number of spectrum elements per CU that
-  // falls with that factor (columns: up to 2, up to 4, above) and grows with
+  // falls with that factor (columns: up to 2.2, up to 4.4, above) and grows with
   // the contraction, which both do alike (one block / three kernels): L=0 N=128
   // C=16 B=128 7.9 / 13.5, B=512 30.0 / 20.1; L=1 N=64 C=64 B=32 7.7 / 14.9, B=128
   // 24.6 / 22.7; L=2 N=256 C=32 B=8 21.0 / 21.1, B=32 38.1 / 27.2; L=4 N=32 C=32
@@ -149,20 +149,20 @@ SmallShape small_shape(int64_t B, int64_t rows, int64_t Nf, int L, int64_t C, in
   // 67.2.  From L_max 3 rows of more than 64 channels stay with the three kernels
   // once the blocks outnumber the CUs (B=64 N=16 L=5 C=100, both gradients 119 /
   // 96; below, L=2 B=16 N=64 C=100 14.6 / 19.9).
-  static constexpr int kMost[7][3] = {{2600, 2200, 1200},  {10000, 7000, 4200},  {26000, 10000, 3500},
+  static constexpr int kMost[7][3] = {{2600, 2200, 1200},  {10000, 7000, 4200},  {26000, 9500, 4500},
                                       {26000, 7500, 4500}, {26000, 11000, 6400}, {24000, 11000, 6400},
                                       {24000, 11000, 6400}};
   if (L >= 3 && C > 64 && B * groups(cc) > kSmallFewBlocks) return r;
   double reread = (double)line / cc;
   if (rows < Nf) reread = 1 + (reread - 1) * (double)rows / (double)Nf;
   reread *= (double)(groups(cc) * cc) / (double)C;
-  double most = kMost[L][reread <= 2 ? 0 : (reread <= 4 ? 1 : 2)];
+  double most = kMost[L][reread <= 2.2 ? 0 : (reread <= 4.4 ? 1 : 2)];
   if (n == 2) {
     most *= 1.45;  // six launches in place of three (L=2 N=256 C=64 B=8: 40.4 / 53.6, one gradient 26.9 / 25.5)
   } else if (Nf >= 128 && L >= 3) {
     // long columns of many components are serial work of few lanes: never where
     // little of a line is used (B=1 N=256 L=3 C=16 25.0 / 20.5), less at 256 rows
-    if (reread > (Nf == 256 ? 4 : 6)) return r;
+    if (reread > (Nf == 256 ? 4 : 7)) return r;
     if (Nf == 256) most *= 0.75;
   }
   r.use = (double)(B * C * K) * 0.5 * (double)(rows + Nf) < 256.0 * most;
