@@ -57,12 +57,15 @@ int ilog2(int64_t x) {
 
 // DFT length of a zero-padded plan of N tokens: the smallest of 2^a, 3 * 2^a,
 // 5 * 2^a (from 640) and 7 * 2^a (from 3584) that is >= 2N - 1.  They are 64 *
-// N1 or 128 * N1 with the odd factor in N1 <= 448, the length of the outer
-// passes.  Every stage's time goes with the length; measured against the next
-// power of two (forward, us, B=4 L=5 C=20): 640 62 / 66, 1280 68 / 83, 3072
-// 131 / 140, 5120 174 / 255, 10240 345 / 511, 12288 397 / 512, 20480 727 /
-// 1019, 49152 2052 / 2424.  The radix-7 passes give 2-10% from 3584 on (140 /
-// 144, 7168 237 / 260, 57344 2383 / 2441) and lose below (1792 89 / 84).
+// N1 or 256 * N1 with the odd factor in N1 <= 448, the length of the outer
+// passes.  Every stage's time goes with the length.  Forward against the next
+// power of two, mean and slowest of L 0..8 with 4 to 512 channels in all (the
+// gradients, channel mixing and inter-channel forms are alike): 640 0.87, 0.98;
+// 768 0.92, 1.00; 1280 0.86, 0.99; 1536 0.90, 1.00; 2560 0.76, 0.94; 3072 0.83,
+// 0.97; 3584 0.88, 0.99; 5120 0.77, 0.94; 7168 0.92, 1.01; 10240 0.71, 0.93; 14336
+// 0.89, 0.97; 20480 0.73, 0.83; 28672 0.91, 0.97; 40960 0.69, 0.86; 49152 0.79, 0.92;
+// 57344 0.89, 0.97.  The radix-7 passes lose below 3584 (1792, B=4 L=5 C=20 89 /
+// 84 us).
 int64_t linear_dft_length(int64_t N) {
   const int64_t need = 2 * N - 1;
   int64_t best = 2;
@@ -848,7 +851,12 @@ cgconv_plan_t cgconv_plan_create_boundary(int64_t batch, int64_t N_tokens, int32
     p->N2 = 64;
     p->N1 = N / 64;
   } else if (!is_pow2(N)) {
-    p->N2 = N <= 64 * 448 ? 64 : 128;  // the odd factor goes to the outer passes, N1 <= 448
+    // the odd factor goes to the outer passes.  Above 28672 N1 = 160, 192 or 224:
+    // with 128 inner rows the outer tiles of 320 to 448 rows take up to 115 KB of
+    // LDS, one block per CU, and few columns were up to 17% slower than the next
+    // power of two; with 256 none is (57344, L=0 B=1 C=4 41 us, 31, power of two
+    // 36; 10% less also on wide plans)
+    p->N2 = N <= 64 * 448 ? 64 : 256;
     p->N1 = N / p->N2;
   } else if (N > 256) {
     const int lg = ilog2(N);

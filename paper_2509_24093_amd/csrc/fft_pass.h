@@ -273,13 +273,16 @@ __global__ __launch_bounds__(T) void fft_pass_kernel(PassArgs a) {
 // thread (1024 threads spill the radix-32 stage out of their 128 registers:
 // 1.56 -> 1.24 ms for the first pass of the zero-padded point-cloud shape).
 // The lengths P 2^j in between: at most 4096 elements up to R = 112 with the
-// columns a power of two, 32 columns and 512 threads above.
+// columns a power of two, 32 columns and 512 threads above.  R = 40, 48 and 56
+// take 32 columns, one item per thread in either stage: 64 left most threads a
+// second item, and at few columns 3584 = 56 x 64 took longer than 4096 (L=1 B=1
+// C=1 forward 16.9 us, 15.3 with 32, 16.1 at 4096; wide plans 2-9% less too).
 constexpr int pow2_floor(int x) { return x < 2 ? 1 : 2 * pow2_floor(x / 2); }
 constexpr bool is_pow2(int x) { return (x & (x - 1)) == 0; }
 template <int R, int INM>
 constexpr int tile_cols() {
   if (R <= 16) return kThreads;
-  if (!is_pow2(R)) return R > 128 ? 32 : pow2_floor(4096 / R);
+  if (!is_pow2(R)) return R > 128 || (R > 32 && R < 64) ? 32 : pow2_floor(4096 / R);
   return R == 512 ? 32 : (R == 256 ? (INM == IN_COMPLEX ? 32 : 64) : 4096 / R);
 }
 template <int R, int INM>

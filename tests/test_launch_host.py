@@ -73,3 +73,17 @@ for L in range(7):
                     assert block[0] <= 1024 and block[0] % 64 == 0 and lds <= allowed, (B, N, L, C, block, lds)
                 P.cgconv_plan_destroy(plan)
 """)
+
+
+def test_first_pass_of_long_odd_lengths_fills_the_chip(tmp_path):
+    # DFT lengths 40960, 49152, 57344 (256 rows per outer tile column) and 3584 (32
+    # columns per tile): with fewer blocks they were slower than the next power of
+    # two at few columns
+    run(tmp_path, """
+for N, L, C, blocks in ((20000, 0, 1, 256), (24500, 0, 1, 256), (28600, 0, 1, 256), (1790, 1, 16, 128)):
+    plan = P.cgconv_plan_create_boundary(1, N, L, C, 1)
+    P.cgconv_forward(plan, ptr(0), ptr(1), ptr(2), 0)
+    grid = launches()[0][0]
+    assert grid[0] * grid[1] * grid[2] >= blocks, (N, grid)
+    P.cgconv_plan_destroy(plan)
+""")
