@@ -280,9 +280,18 @@ def dft_length(N, boundary):
 KERNEL_OF_STAGE = {"cg_fused": "cg_fused_kernel", "cg_small": "cg_small_kernel"}
 
 
-def cg_roofline(stage_avg, B, N, L, C, n_products, nnz, traffic, traffic_src):
+def backward_stages(stage_avg):
+    """What one timed call of a backward holds: the key its stages are reported
+    under and the number of convolutions.  The three-kernel and two-pass plans
+    time each gradient as a call of its own; the one-block kernel runs both
+    gradients in one launch, one timed call."""
+    return ("stages_both_gradients", 2) if "cg_small" in stage_avg else ("stages_per_gradient", 1)
+
+
+def cg_roofline(stage_avg, B, N, L, C, n_products, nnz, traffic, traffic_src, convolutions=1):
     """Roofline object of the CG stage (fused or unfused) from its average
-    launch time: algorithmic flops per launch against the fp32 vector peak."""
+    launch time: algorithmic flops per launch of that many convolutions
+    against the fp32 vector peak."""
     K = (L + 1) ** 2
     Cp = (C + 1) // 2
     F = N // 2 + 1
@@ -307,6 +316,9 @@ def cg_roofline(stage_avg, B, N, L, C, n_products, nnz, traffic, traffic_src):
         dft = 5 * N * (N.bit_length() - 1)
         flops += dft * B * K * (C + Cp)
         flop_model += f" + {dft}-flop length-{N} DFTs on {B * K * (C + Cp)} columns"
+    if convolutions > 1:
+        flops *= convolutions
+        flop_model = f"{convolutions} x ({flop_model})"
     achieved_tflops = flops / (cg_ms * 1e-3) / 1e12
     return {
         "kernel": f"{KERNEL_OF_STAGE.get(dom) or ('cg_split_kernel' if L >= 7 else 'cg_gen_kernel')}<{L}>",
@@ -689,7 +701,8 @@ def _timed(args, step, plan, calls_per_step=1):
 def bench_backward(args, plan, q, k, qd, kd, B, N, L, C):
     """cgconv_backward (both gradients) for a seeded output gradient ~ N(0, 1).
     Each gradient is one forward-shaped pipeline on the same kernels, so the
-    stage times are averages over the 2 * steps pipelines."""
+    stage times are averages over the 2 * steps pipelines; where the one-block
+    kernel runs both gradients in one launch, over the steps."""
     import numpy as np
     import torch
 
@@ -708,12 +721,14 @@ def bench_backward(args, plan, q, k, qd, kd, B, N, L, C):
     counters, src = committed_counters(args.workload)
     if args.boundary != "cyclic":
         counters, src = None, "counters were taken with the cyclic boundary"
+    stages_key, convolutions = backward_stages(stage_avg)
     roofline = cg_roofline(stage_avg, B, dft_length(N, args.boundary), L, C, n_products, nnz,
                            counters["cg_hbm_bytes_per_launch"] if counters else None,
-                           (src + "; taken on the forward, same kernel and launch shape") if counters else src)
+                           (src + "; taken on the forward, same kernel and launch shape") if counters else src,
+                           convolutions=convolutions)
     result = _common(args, METRIC_BACKWARD, ms, B, N, L, C, "f32", timing)
     result["roofline"] = roofline
-    result["stages_per_gradient"] = {s: {"ms": round(t, 4)} for s, t in stage_avg.items()}
+    result[stages_key] = {s: {"ms": round(t, 4)} for s, t in stage_avg.items()}
     if not args.no_cpu_baseline:
         from oracle.backward import backward_direct_rows
         log(f"[bench] CPU oracle baseline, backward (~{args.cpu_seconds:.0f} s)")

@@ -368,19 +368,22 @@ int cgconv_contract_host(int32_t L_max, const double* qhat, const double* khat, 
 
 /*
  * Per-stage timing for profiling.  After cgconv_plan_enable_timing(plan, n),
- * the next n forwards of the plan record HIP events before and after each
+ * the next n calls of the plan record HIP events before and after each
  * kernel stage on the forward's own stream (a few microseconds per call);
  * calls beyond n are not timed.  Enabling again resets the record.
  * cgconv_plan_stage_times waits for the timed calls to finish and writes the
  * summed time of each stage in milliseconds to ms[0 .. min(cap, n_stages)-1];
- * n_stages and n_calls (may be NULL) receive the stage count (3 for N <= 256:
- * fft_fwd, cg, fft_inv; 5 above: fft_fwd_1, fft_fwd_2, cg, fft_inv_1,
- * fft_inv_2; for plans with 512 <= N <= 32768 and L_max <= 6: fft_fwd_1,
- * cg_fused, fft_inv_2) and the number of timed calls.  The first timed call
- * fixes which kind is timed: plain forwards, mixed forwards (cg_mix replaces
- * cg and the unfused passes are listed), inter-channel forwards (cg_inter
- * likewise), backwards (each of the two
- * gradients is one timed call with the plain stages), gating calls
+ * n_stages and n_calls (may be NULL) receive the stage count and the number of
+ * timed calls.  The stages of a plain forward, by DFT length: 1 (cg_small)
+ * where the one-block kernel runs it, which takes lengths up to 256 at L_max <=
+ * 6; else 3 up to 256 (fft_fwd, cg, fft_inv), 3 for 512 .. 32768 at L_max <= 6
+ * (fft_fwd_1, cg_fused, fft_inv_2) and 5 otherwise (fft_fwd_1, fft_fwd_2, cg,
+ * fft_inv_1, fft_inv_2).  The first timed call fixes which kind is timed: plain
+ * forwards, mixed forwards (cg_mix replaces cg and the unfused passes are
+ * listed), inter-channel forwards (cg_inter likewise), backwards (each of the
+ * two gradients is one timed call with the stages of a forward of the three or
+ * five kernels), backwards of the one-block kernel (all gradients asked for are
+ * one launch, one timed call with the single stage cg_small), gating calls
  * (gate_partials, gate_finalize, gate_value), gating backwards (gate_stats,
  * gate_bwd, gate_sums, gate_bwd_du) or graph forwards
  * (gft_split_u, gft_split_x, gft_gemm_fwd, gft_product, gft_split_uhat,

@@ -49,3 +49,8 @@ def test_roofline_of_each_cg_stage():
     r = bench.cg_roofline({"cg_small": 0.02}, Bs, Ns, Ls, Cs, 555, 1392, None, "none")
     assert r["kernel"] == "cg_small_kernel<4>"
     assert r["flops_per_launch"] == _model(Bs * (Ns // 2 + 1) * Cs, 555, 1392) + 5 * Ns * 5 * Bs * 25 * (Cs + 16)
+    # a backward of the one-block kernel: both gradients in the timed launch
+    assert bench.backward_stages({"cg_small": 0.02}) == ("stages_both_gradients", 2)
+    assert bench.backward_stages({"fft_fwd": 0.1, "cg": 0.1, "fft_inv": 0.1}) == ("stages_per_gradient", 1)
+    both = bench.cg_roofline({"cg_small": 0.02}, Bs, Ns, Ls, Cs, 555, 1392, None, "none", convolutions=2)
+    assert both["flops_per_launch"] == 2 * r["flops_per_launch"] and abs(both["frac"] - 2 * r["frac"]) < 2e-4

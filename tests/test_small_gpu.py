@@ -58,3 +58,18 @@ def test_one_block_forward_and_gradients(shape):
         err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
         assert err <= TOL, err
     plan.close()
+
+
+def test_timed_backward_of_the_one_block_kernel_is_one_call():
+    torch = pytest.importorskip("torch")
+    import paper_2509_24093_amd as P
+    for L, gradients, calls, stages in ((4, 2, 1, ["cg_small"]), (4, 1, 1, ["cg_small"]),
+                                        (7, 2, 2, ["fft_fwd", "cg", "fft_inv"])):
+        plan = P.Plan(32, 32, L, 4)
+        q, k, g = (torch.randn(plan.shape, device="cuda") for _ in range(3))
+        P.cgconv_plan_enable_timing(plan._h, 8)
+        print(f"[gpu] timed backward L={L} gradients={gradients}", flush=True)
+        plan.backward(q, k, g, need_k=gradients == 2)
+        times, n = P.cgconv_plan_stage_times(plan._h)
+        plan.close()
+        assert n == calls and list(times) == stages and all(t > 0 for t in times.values())
