@@ -4,11 +4,11 @@ oracle on the same seeded inputs.
 
 Bar: relative L2 error <= 1e-4 (fp32), <= 5e-3 (bf16 storage, oracle on the
 same rounded inputs).  Token counts that are not powers of two and that
-select every pipeline through the DFT length Nf = next power of two >= 2N-1
-(single pass, fused two-pass, unfused two-pass at L >= 7 or Nf > 32768).
-Small N: the oracle's linear direct sums; larger N: the oracle's cyclic FFT
-mode on the inputs zero-padded to Nf, first N rows (an identity pinned in
-tests/test_oracle_linear.py).  Also the backward, gating over the N tokens,
+select every pipeline through the DFT length Nf >= 2N-1 (single pass, fused
+two-pass, unfused two-pass at L >= 7 or Nf > 32768); each length is pinned in
+tests/test_linear_lengths_gpu.py.  Small N: the oracle's linear direct sums;
+larger N: the oracle's cyclic FFT mode on zero-padded inputs, first N rows (an
+identity at any padded length >= 2N-1, pinned in tests/test_oracle_linear.py).  Also the backward, gating over the N tokens,
 channel mixing, bf16 storage and argument errors.
 """
 
@@ -34,6 +34,7 @@ def _torch():
 
 
 def _nf(N):
+    """Length the oracle pads to (the library's may be shorter)."""
     n = 2
     while n < 2 * N - 1:
         n *= 2
@@ -56,12 +57,12 @@ def _ref_forward(q, k, L):
 
 def _plan(B, N, L, C, tag):
     import paper_2509_24093_amd as P
-    print(f"[gpu] {tag} linear plan B={B} N={N} (DFT length {_nf(N)}) L={L} C={C}", flush=True)
+    print(f"[gpu] {tag} linear plan B={B} N={N} L={L} C={C}", flush=True)
     return P.Plan(B, N, L, C, boundary="linear")
 
 
-# (B, N, L, C) -> DFT length: 2, 8, 256 (single pass), 512 / 2048 / 16384 /
-# 32768 (fused), 1024 at L=8 and 65536 (unfused two-pass)
+# (B, N, L, C) -> DFT length: 2, 8, 256 (single pass), 512 / 2048 / 10240 /
+# 16384 / 24576 (fused), 640 at L=8 and 40960 (unfused two-pass)
 SHAPES = [(1, 1, 2, 3), (2, 3, 1, 2), (1, 100, 3, 5), (1, 200, 6, 2), (2, 1000, 4, 3), (1, 5000, 2, 4),
           (1, 8192, 6, 2), (1, 12000, 6, 3), (1, 300, 8, 2), (1, 20000, 1, 2)]
 

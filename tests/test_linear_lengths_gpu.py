@@ -2,7 +2,8 @@
 two would overshoot): every outer-pass radix, the fused pipeline, the unfused
 one (L_max 7, lengths above 32768) and the stages that keep spectra between
 passes (channel mixing, inter-channel), against the oracle's cyclic FFT mode
-on padded inputs (any padded length >= 2N - 1 gives the linear sums).
+on padded inputs (any padded length >= 2N - 1 gives the linear sums).  Then
+the powers of two that zero-padded plans still take.
 
 Tolerance: fp32 DFTs and sums, a few 2^-24 sqrt(log2 N); bar 2e-6.  The mixed
 form multiplies bfloat16 high and low parts: 2e-5.
@@ -93,3 +94,27 @@ def test_mixed_and_interchannel(N):
     plan.close()
     assert _err(mixed, cgconv_mixed_fft(wide[0], wide[1], L, w)[:, :N]) <= TOL_MIXED
     assert _err(inter, cgconv_interchannel(wide[0], wide[1], L, heads, wi, mode="fft")[:, :N]) <= TOL
+
+
+# 2048 fused, 32768 fused with outer passes of 512, 65536 unfused, 1024 unfused at L_max 8
+@pytest.mark.parametrize("N,length,L,C", [(1000, 2048, 2, 3), (14337, 32768, 1, 2), (16384, 32768, 1, 2),
+                                          (28673, 65536, 1, 2), (32768, 65536, 0, 3), (400, 1024, 8, 2)])
+def test_power_of_two_lengths(N, length, L, C):
+    torch = pytest.importorskip("torch")
+    import paper_2509_24093_amd as P
+    (q, k, g), wide = _case(1, N, L, C, N)
+    print(f"[gpu] linear N={N} length {length} L={L}", flush=True)
+    dev = [torch.from_numpy(a).cuda() for a in (q, k, g)]
+    plan = P.Plan(1, N, L, C, boundary="linear")
+    out = plan(dev[0], dev[1])
+    gq, gk = plan.backward(*dev)
+    bf = plan(dev[0].bfloat16(), dev[1].bfloat16())
+    torch.cuda.synchronize()
+    spectra = 2 * 8 * (L + 1) ** 2 * C  # the workspace holds two spectra of the DFT length
+    assert spectra * length <= plan.info()[2] < spectra * (length + 512) + 64 * N * (L + 1) * C
+    plan.close()
+    rq, rk = backward_fft(*wide, L)
+    ref = cgconv_fft(wide[0], wide[1], L)[:, :N]
+    assert _err(out, ref) <= TOL
+    assert _err(gq, rq[:, :N]) <= TOL and _err(gk, rk[:, :N]) <= TOL
+    assert np.linalg.norm(bf.float().cpu().numpy() - ref) <= 1e-2 * np.linalg.norm(ref)
