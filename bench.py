@@ -266,15 +266,19 @@ def cpu_fft_baseline(q, k, L, budget_s, got):
 
 
 def dft_length(N, boundary):
-    """Length of the token DFTs: N (cyclic) or the smallest power of two
-    >= 2N - 1 (zero-padded boundary; the library's length for the benchmark's
-    token counts, which are powers of two)."""
+    """Length of the token DFTs: N (cyclic), or with the zero-padded boundary the
+    smallest of 2^a, 3 * 2^a and 5 * 2^a (from 640) and 7 * 2^a (from 3584) that
+    is >= 2N - 1, the library's rule."""
     if boundary == "cyclic":
         return N
-    n = 2
-    while n < 2 * N - 1:
-        n *= 2
-    return n
+    lengths = [2]
+    while lengths[-1] < 2 * N - 1:
+        lengths.append(2 * lengths[-1])
+    for first in (768, 640, 3584) if 2 * N - 1 > 512 else ():
+        while first < 2 * N - 1:
+            first *= 2
+        lengths.append(first)
+    return min(n for n in lengths if n >= 2 * N - 1)
 
 
 KERNEL_OF_STAGE = {"cg_fused": "cg_fused_kernel", "cg_small": "cg_small_kernel"}

@@ -20,8 +20,10 @@ def test_more_than_one_gpu_exits_with_a_message():
 
 def test_dft_length():
     assert [bench.dft_length(n, "cyclic") for n in (2, 64, 16384)] == [2, 64, 16384]
-    # zero padding: the smallest power of two >= 2N - 1
+    # zero padding: powers of two, and 3, 5 and 7 times one from 640 on
     assert [bench.dft_length(n, "linear") for n in (1, 2, 3, 100, 16384)] == [2, 4, 8, 256, 32768]
+    assert [bench.dft_length(n, "linear") for n in (256, 257, 320, 321, 1025, 1793, 5000, 28672)] == [
+        512, 640, 640, 768, 2560, 4096, 10240, 57344]
 
 
 def _model(points, n_products, nnz):

@@ -87,3 +87,16 @@ for N, L, C, blocks in ((20000, 0, 1, 256), (24500, 0, 1, 256), (28600, 0, 1, 25
     assert grid[0] * grid[1] * grid[2] >= blocks, (N, grid)
     P.cgconv_plan_destroy(plan)
 """)
+
+
+def test_dft_lengths_are_the_benchmarks(tmp_path):
+    # unfused plans: the groups of the first two passes are the two factors of the length
+    run(tmp_path, """
+import bench
+for N in list(range(257, 400)) + list(range(500, 32769, 487)) + [1024, 1025, 1792, 1793, 14336, 14337, 20480, 28672, 28673, 32768]:
+    plan = P.cgconv_plan_create_boundary(1, N, 7, 1, 1)
+    P.cgconv_forward(plan, ptr(0), ptr(1), ptr(2), 0)
+    first, second = (l[0][1] for l in launches()[:2])
+    assert first * second == bench.dft_length(N, "linear"), (N, first, second)
+    P.cgconv_plan_destroy(plan)
+""")
