@@ -650,6 +650,7 @@ struct PairsTable {
   std::vector<std::array<float, 4>> slots;  // [slot][2 h + row degree]
 };
 constexpr size_t kPairsSlots = 16;  // slots of one pipeline stage
+constexpr int kPairsLmax = 6;       // highest L_max with an inter-channel kernel
 
 void emit_pairs_body(FILE* f, int L, long* ops_out, long* mfma_out) {
   const int K = (L + 1) * (L + 1);
@@ -1040,12 +1041,15 @@ int main(int argc, char** argv) {
     emit_real_body(f, L, &rops);
     emit_mirror_body(f, L, &sops);
     emit_path_split_body(f, L, &psops);
-    long pops = 0, pmfma = 0;
-    std::fprintf(f, "#ifdef CGCONV_PAIRS_BODY  // the inter-channel kernel only\n");
-    emit_pairs_body(f, L, &pops, &pmfma);
-    std::fprintf(f, "#endif\n");
+    if (L <= kPairsLmax) {
+      long pops = 0, pmfma = 0;
+      std::fprintf(f, "#ifdef CGCONV_PAIRS_BODY  // the inter-channel kernel only\n");
+      emit_pairs_body(f, L, &pops, &pmfma);
+      std::fprintf(f, "#endif\n");
+      std::fprintf(stderr, "gen_cg: L=%d channel-pairs body: %ld ops and %ld matrix instructions per wave\n", L, pops,
+                   pmfma);
+    }
     std::fclose(f);
-    std::fprintf(stderr, "gen_cg: L=%d channel-pairs body: %ld ops and %ld matrix instructions per wave\n", L, pops, pmfma);
     std::fprintf(stderr,
                  "gen_cg: L=%d ops/point=%ld real token-wise ops=%ld mirror lane-pair ops/lane=%ld "
                  "per-path lane-pair ops/lane=%ld\n",

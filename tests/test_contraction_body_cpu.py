@@ -4,6 +4,8 @@ float and compared with the plan's host contraction of the same table
 (cgconv_contract_host), which is itself pinned to the oracle's dense tensor.
 The mirror lane-pair body runs with both lanes of a point side by side: a
 value is a pair of doubles, one per lane, and the lane swap exchanges them.
+The channel-pairs body runs with the 64 lanes of a wave side by side: a value
+is 64 doubles, the 4x4x1 matrix instruction its 16 outer products.
 """
 
 import ctypes
@@ -148,3 +150,127 @@ def test_real_body_is_the_real_table(L, bodies):
         lib.real(_ptr(a), _ptr(b), _ptr(f))
         ref = np.bincount(o, weights=coef * a[x] * b[y], minlength=K)
         assert np.abs(f - ref).max() < 2e-7 * np.abs(ref).max() * np.sqrt(K)
+
+
+# A wave of the inter-channel kernel: lane = c2 * 8 + c1.  The matrix
+# instruction's blocks are groups of four lanes; A holds a row per lane, B a
+# column per lane, D[r] row r of the lane's column.  cbsz = 1 takes A from block
+# abid of each pair of blocks.
+PAIRS_PRELUDE = r"""
+#include <array>
+#include <vector>
+#define __device__
+#define __forceinline__ inline
+#define __builtin_amdgcn_sched_barrier(x)
+#define __builtin_amdgcn_mfma_f32_4x4x1f32 mfma441
+struct W {
+  std::vector<double> v;
+  W() : v(64) {}
+  W(double x) : v(64, x) {}
+};
+template <class F> static W each(F f) { W r; for (int i = 0; i < 64; ++i) r.v[i] = f(i); return r; }
+static W operator*(const W& x, const W& y) { return each([&](int i) { return x.v[i] * y.v[i]; }); }
+static W operator+(const W& x, const W& y) { return each([&](int i) { return x.v[i] + y.v[i]; }); }
+static W operator-(const W& x, const W& y) { return each([&](int i) { return x.v[i] - y.v[i]; }); }
+static W operator-(const W& x) { return each([&](int i) { return -x.v[i]; }); }
+static W vfma(const W& x, const W& y, const W& z) { return each([&](int i) { return x.v[i] * y.v[i] + z.v[i]; }); }
+#define float W
+#define fmaf vfma
+struct float2 { W x, y; };
+static float2 make_float2(const W& x, const W& y) { return {x, y}; }
+struct v4f {
+  std::array<W, 4> e;
+  v4f() {}
+  v4f(double a, double b, double c, double d) : e{W(a), W(b), W(c), W(d)} {}
+  W& operator[](int i) { return e[i]; }
+};
+static v4f mfma441(const W& a, const W& b, v4f c, int cbsz, int abid, int) {
+  for (int r = 0; r < 4; ++r)
+    for (int l = 0; l < 64; ++l) {
+      const int block = l / 4, from = (block >> cbsz << cbsz) + (cbsz ? abid : block & ((1 << cbsz) - 1));
+      c.e[r].v[l] += a.v[4 * from + r] * b.v[l];
+    }
+  return c;
+}
+template <int L> struct CgBody;
+template <int L> struct CgRealBody;
+template <int L> struct CgMirrorBody;
+template <int L> struct CgPathSplitBody;
+template <int L> struct CgPairsBody;
+#define CGCONV_PAIRS_BODY
+"""
+
+PAIRS_DRIVER = r"""
+struct Tab {  // entry e: four coefficients of each of the four lane roles
+  const double* t;
+  Tab fresh() const { return *this; }
+  v4f at(int e) const {
+    v4f r;
+    for (int i = 0; i < 4; ++i)
+      r.e[i] = each([&](int l) { return t[16 * e + 4 * (((l >> 2) & 1) * 2 + ((l >> 1) & 1)) + i]; });
+    return r;
+  }
+};
+struct PStore {
+  double* out;  // [K][64] complex
+  int phases = 0;
+  void operator()(int k, const float2& u) {
+    for (int l = 0; l < 64; ++l) { out[2 * (64 * k + l)] = u.x.v[l]; out[2 * (64 * k + l) + 1] = u.y.v[l]; }
+  }
+  void end_phase(int mu) { phases = phases == mu ? mu + 1 : -1000; }
+};
+// q, k: [8 channels][K] complex, 2Q and 2K in the complex-m basis; degrees of odd l times i
+extern "C" int pairs(const double* q, const double* k, const double* table, double* out) {
+  constexpr int K = (LL + 1) * (LL + 1);
+  float2 qa[K];
+  W kp[K];
+  for (int l = 0; l <= LL; ++l)
+    for (int i = l * l; i < (l + 1) * (l + 1); ++i)
+      for (int lane = 0; lane < 64; ++lane) {
+        const double *a = q + 2 * (K * (lane & 7) + i), *b = k + 2 * (K * (lane >> 3) + i);
+        const bool im = lane & 1, odd = l & 1;
+        qa[i].x.v[lane] = odd ? -a[1] : a[0];
+        qa[i].y.v[lane] = odd ? a[0] : a[1];
+        kp[i].v[lane] = odd ? (im ? b[0] : -b[1]) : (im ? b[1] : b[0]);
+      }
+  PStore st{out};
+  CgPairsBody<LL>::run(qa, kp, Tab{table}, st);
+  return st.phases == LL + 1 ? CgPairsBody<LL>::kEntries : -1;
+}
+"""
+
+
+@pytest.mark.parametrize("L", [0, 1, 2, 3, 6])
+def test_pairs_body_is_the_host_contraction_of_every_pair(L, tmp_path):
+    subprocess.run(["g++", "-O1", "-std=c++17", os.path.join(CSRC, "codegen", "gen_cg.cpp"),
+                    os.path.join(CSRC, "cg_table.cpp"), "-o", str(tmp_path / "gen")], check=True)
+    subprocess.run([str(tmp_path / "gen"), str(tmp_path), "8"], check=True, capture_output=True)
+    body = (tmp_path / f"cg_body_L{L}.inc").read_text().split("#ifdef CGCONV_PAIRS_BODY")[1].split("\n", 1)[1]
+    code, rest = body.split("static __device__ __attribute__((aligned(16))) const float pairs_table", 1)
+    numbers = rest[rest.index("{") + 1:rest.index("}")].replace("f", "").replace("\n", "")
+    table = np.array([float(x) for x in numbers.split(",") if x.strip()])
+    src, so = tmp_path / "pairs.cpp", tmp_path / "pairs.so"
+    src.write_text(PAIRS_PRELUDE + f"#define LL {L}\n" + code + "\n#undef float\n" + PAIRS_DRIVER)
+    subprocess.run(["g++", "-O0", "-std=c++17", "-w", "-fno-exceptions", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    lib = ctypes.CDLL(str(so))
+    rng = np.random.default_rng(90 + L)
+    K = (L + 1) ** 2
+    q = rng.normal(size=(8, K)) + 1j * rng.normal(size=(8, K))
+    k = rng.normal(size=(8, K)) + 1j * rng.normal(size=(8, K))
+    qa, ka = (np.array([_complex_basis(L, x) for x in a]) for a in (q, k))
+    out = np.zeros((K, 64), dtype=np.complex128)
+    assert lib.pairs(_ptr(qa), _ptr(ka), _ptr(table), _ptr(out)) == len(table) // 16
+    for c1 in range(8):
+        for c2 in range(8):
+            ref = P.cgconv_contract_host(L, q[c1], k[c2])
+            # the coefficients are rounded to float (2^-24 each)
+            assert np.abs(out[:, 8 * c2 + c1] - ref).max() < 2e-7 * np.abs(ref).max() * np.sqrt(K), (c1, c2)
+
+
+def test_pairs_bodies_end_at_the_inter_channel_kernels(tmp_path):
+    from paper_2509_24093_amd import build
+    subprocess.run(["g++", "-O1", "-std=c++17", os.path.join(CSRC, "codegen", "gen_cg.cpp"),
+                    os.path.join(CSRC, "cg_table.cpp"), "-o", str(tmp_path / "gen")], check=True)
+    subprocess.run([str(tmp_path / "gen"), str(tmp_path), "8"], check=True, capture_output=True)
+    emitted = [L for L in range(9) if "CgPairsBody" in (tmp_path / f"cg_body_L{L}.inc").read_text()]
+    assert emitted == list(range(build.INTER_LMAX + 1))
