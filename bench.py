@@ -762,18 +762,24 @@ def bench_backward(args, plan, q, k, qd, kd, B, N, L, C):
     print(json.dumps(result), flush=True)
 
 
+def value_product_flops(n_products, nnz):
+    """Flops of one token-wise CG product of real components: the kernels take
+    it in the complex-m basis, where real inputs leave half of the complex
+    products and terms (those of M < 0 are conjugates), i.e. two real flops per
+    complex-basis term and one per product."""
+    return n_products + 2 * nnz
+
+
 def bench_gate(args, plan, q, k, qd, kd, out, B, N, L, C):
     """cgconv_gate_value with u = q and v = k of the workload."""
     import numpy as np
 
-    import paper_2509_24093_amd as P
     log(f"[bench] timing {args.steps} gating steps")
     ms, stage_avg, timing = _timed(args, lambda: plan.gate_value(qd, kd, out), plan)
     K = (L + 1) ** 2
-    _, coef = P.cgconv_cg_table(L)
-    nnz_real = len(coef)
+    nnz, n_products = plan.contraction_info()
     lanes = B * N * C
-    per_lane = K * K + 2 * nnz_real + 3 * K
+    per_lane = value_product_flops(n_products, nnz) + 3 * K
     flops = per_lane * lanes
     gv_ms = stage_avg["gate_value"]
     achieved = flops / (gv_ms * 1e-3) / 1e12
@@ -787,9 +793,9 @@ def bench_gate(args, plan, q, k, qd, kd, out, B, N, L, C):
         "frac": round(achieved / VALU_PEAK_TFLOPS, 4),
         "traffic": None,
         "flops_per_launch": flops,
-        "flop_model": (f"per (b, i, c) lane: {K}^2 products u_x v_y + 2 flops (multiply-add by the "
-                       f"coefficient) per real-basis non-zero ({nnz_real}) + 3K for the norms and the gate; "
-                       f"{lanes} lanes"),
+        "flop_model": (f"per (b, i, c) lane: the CG product of real components in the complex-m basis, "
+                       f"{n_products} products + 2 flops (multiply-add by the coefficient) per non-zero ({nnz}), "
+                       f"+ 3K for the norms and the gate; {lanes} lanes"),
         "algorithmic_bytes_per_launch": 3 * K * 4 * lanes,
         "achieved_gbs": round(3 * K * 4 * lanes / (gv_ms * 1e-3) / 1e9, 1),
         "launch_ms": round(gv_ms, 4),
@@ -841,10 +847,9 @@ def bench_gate_backward(args, plan, q, k, qd, kd, B, N, L, C):
     log(f"[bench] timing {args.steps} gating backward steps")
     ms, stage_avg, timing = _timed(args, step, plan)
     K = (L + 1) ** 2
-    _, coef = P.cgconv_cg_table(L)
-    nnz_real = len(coef)
+    nnz, n_products = plan.contraction_info()
     lanes = B * N * C
-    per_lane = 2 * (K * K + 2 * nnz_real) + 8 * K
+    per_lane = 2 * value_product_flops(n_products, nnz) + 8 * K
     flops = per_lane * lanes
     bw_ms = stage_avg["gate_bwd"]
     achieved = flops / (bw_ms * 1e-3) / 1e12
@@ -858,9 +863,9 @@ def bench_gate_backward(args, plan, q, k, qd, kd, B, N, L, C):
         "frac": round(achieved / VALU_PEAK_TFLOPS, 4),
         "traffic": None,
         "flops_per_launch": flops,
-        "flop_model": (f"per (b, i, c) lane: two real-basis tensor products (one per gradient), each {K}^2 "
-                       f"products + 2 flops per non-zero ({nnz_real}), + 8K for the scales, the gate and "
-                       f"its sums; {lanes} lanes"),
+        "flop_model": (f"per (b, i, c) lane: two CG products of real components in the complex-m basis (one per "
+                       f"gradient), each {n_products} products + 2 flops per non-zero ({nnz}), + 8K for the scales, "
+                       f"the gate and its sums; {lanes} lanes"),
         "algorithmic_bytes_per_launch": 5 * K * 4 * lanes,
         "achieved_gbs": round(5 * K * 4 * lanes / (bw_ms * 1e-3) / 1e9, 1),
         "launch_ms": round(bw_ms, 4),

@@ -56,3 +56,9 @@ def test_roofline_of_each_cg_stage():
     assert bench.backward_stages({"fft_fwd": 0.1, "cg": 0.1, "fft_inv": 0.1}) == ("stages_per_gradient", 1)
     both = bench.cg_roofline({"cg_small": 0.02}, Bs, Ns, Ls, Cs, 555, 1392, None, "none", convolutions=2)
     assert both["flops_per_launch"] == 2 * r["flops_per_launch"] and abs(both["frac"] - 2 * r["frac"]) < 2e-4
+
+
+def test_flops_of_the_value_product():
+    # L_max 6: 2149 distinct products, 7396 complex-basis terms; the generated body
+    # runs 8850 vector operations, most of them two flops
+    assert bench.value_product_flops(2149, 7396) == 16941 <= 2 * 8850
