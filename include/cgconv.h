@@ -199,8 +199,8 @@ int cgconv_forward_interchannel(cgconv_plan_t plan, int32_t heads, int32_t m_out
  * out must not alias U, q or k.  The dense transforms run on the bfloat16
  * matrix cores with both operands split into high and low parts (relative
  * error about 2^-16 per product, fp32 accumulation); the per-frequency
- * product is the generated real-basis contraction.  Same stream and
- * workspace rules as cgconv_forward.
+ * product is the generated contraction of real components (evaluated in the
+ * complex-m basis).  Same stream and workspace rules as cgconv_forward.
  */
 cgconv_plan_t cgconv_plan_create_graph(int64_t batch, int64_t N, int32_t L_max, int64_t C);
 int cgconv_forward_graph(cgconv_plan_t plan, const float* U, const float* q, const float* k, float* out,
@@ -324,7 +324,8 @@ int cgconv_plan_info(cgconv_plan_t plan, int64_t* n_paths, int64_t* nnz, size_t*
  * number of complex-basis terms (selection rule M = m1 + m2, §4.3) and of
  * distinct complex products q[l1,m1] * k[l2,m2] among them, per frequency
  * and channel.  (A graph plan reports the same counts; its per-frequency
- * product runs on the real-basis entries.)  Either pointer may be NULL.
+ * product has real operands, for which half of them are conjugates of the
+ * other half.)  Either pointer may be NULL.
  */
 int cgconv_plan_contraction_info(cgconv_plan_t plan, int64_t* nnz_complex, int64_t* n_products);
 

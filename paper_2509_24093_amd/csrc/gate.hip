@@ -1,4 +1,4 @@
-// Token-wise real-basis CG products for gfx950: the invariant softmax gating
+// Token-wise CG products of real components for gfx950: the invariant softmax gating
 // with the real-space value tensor product (arXiv 2509.24093, §4.1.1 Invariant
 // Gating, Algorithm 1 step 5), and the product per graph frequency of the
 // graph Fourier variant (appendix "Fourier Space Attention").
@@ -216,9 +216,9 @@ __device__ __forceinline__ constexpr int degree_of(int k) {
 //   da = s_o .* TP(s_a .* G, s_b .* v)   s_a = sqrt(2l+1), s_b = (-1)^l, s_o = 1 / s_a
 //   dv = t_o .* TP(t_a .* G, a)          t_a = (-1)^l sqrt(2l+1), t_o = (-1)^l / sqrt(2l+1)
 // with a = g u (constants of the unrolled code: read from the plan's table,
-// the output scales were vector loads behind the gradient's stores).  DU = false stores dv; DU = true stores du = g da (the gate
-// held fixed) and h[l] = g[l] sum_m u[l,m] da[l,m] for the softmax and norm
-// terms.  The two gradients are separate launches so that each holds only
+// the output scales were vector loads behind the gradient's stores).  DU =
+// false stores dv; DU = true stores du = g da (the gate held fixed) and h[l] =
+// g[l] sum_m u[l,m] da[l,m] for the softmax and norm terms.  The two gradients are separate launches so that each holds only
 // one product's operands and result in registers (3 waves per SIMD at
 // L_max = 6); u is read again for h after the product instead of being held
 // across it.
