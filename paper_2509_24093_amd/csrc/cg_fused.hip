@@ -306,6 +306,17 @@ __global__ __launch_bounds__(kThreadsF, 2) void cg_fused_kernel(FusedArgs a) {
   st.Cp = a.Cp;
   st.even = (cc & 1) == 0;
   st.selfpaired = selfpaired;
+  // The body is tens of kilobytes of straight-line code and is bound by its
+  // fetch: whether most of its 8-byte instructions start at a multiple of 8
+  // bytes or between two costs up to 6 % of the kernel, and any edit above it
+  // moves them all.  So its start is pinned, at the better of the two (whole
+  // transform, fp32, body 0 / 4 bytes past a multiple of 8; N = 4096, B = 3,
+  // C = 14: L = 5 87.4 / 82.4 us, L = 6 128.6 / 126.9; L <= 4, and N = 8192 with
+  // B = 2, C = 32, within what two runs differ).
+  if constexpr (L >= 5)
+    asm volatile(".p2align 3\n\ts_nop 0");
+  else
+    asm volatile(".p2align 3");
   CgBody<L>::run(qa, ka, st);
 }
 
