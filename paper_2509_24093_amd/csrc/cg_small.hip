@@ -30,8 +30,8 @@
 // Bound by latency: one lane's chain of loads, LDS exchanges and dependent
 // operations (of 47k cycles at B=32, N=32, L_max=4, C=32 with one lane group
 // per point, 20k were the contraction's 2.6k operations, which two groups
-// halve).  Measured at that shape: forward 17.8 us (23.4 with the lane pair
-// that held q in one lane and k in the other), both gradients 22.1 us (52.4 in
+// halve).  Measured at that shape: forward 17.5 us (23.6 with the lane pair
+// that held q in one lane and k in the other), both gradients 21.1 us (52.7 in
 // the six launches of the three kernels).
 #include <hip/hip_runtime.h>
 

@@ -220,7 +220,7 @@ __device__ __forceinline__ constexpr int degree_of(int k) {
 // false stores dv; DU = true stores du = g da (the gate held fixed) and h[l] =
 // g[l] sum_m u[l,m] da[l,m] for the softmax and norm terms.  The two gradients are separate launches so that each holds only
 // one product's operands and result in registers (3 waves per SIMD at
-// L_max = 6); u is read again for h after the product instead of being held
+// L_max = 6 for dv, 2 for du); u is read again for h after the product instead of being held
 // across it.
 template <int L, bool DU>
 __global__ __launch_bounds__(kGateThreads) void gate_bwd_kernel(GateBwdArgs a, long long lanes) {
